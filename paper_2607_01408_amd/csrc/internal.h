@@ -247,6 +247,43 @@ hipError_t launch_uvw_grad_x2(const float* x1, const float* g, const float* w, f
                               int W, const uint32_t* table, const uint32_t* table2, int n_blocks2, int n_paths,
                               int nc1, int nc2, int nco, int d1max, int d2max, hipStream_t stream);
 
+// The same product and gradients for blocks up to kUvwzMaxD wide (uvw_blocks.hip).  Table
+// words: header [kUvwzHeader]:
+//   [0] n_paths, [3 + 4 r .. 6 + 4 r] for role r (0: output blocks, stages by x1 block; 1: x1
+//   blocks, stages by output block; 2: x2 blocks, stages by x1 block): first word of the
+//   blocks, their number, first word of the stages, first word of the path references;
+//   [15] first word of the weight gradient's units, [16] their number, [17] first word of
+//   their path references; the others 0.
+// Entry records, d1 x d3 per path ([k1][k3]): kUvwzEntries pairs of (x2 slot, fp32 value),
+// padded with value 0 at slot NC2.  Dense values per path: [k1][k3][k2], fp32.  Path
+// reference (4 words): path index, first word of its records, first word of its dense
+// values, its output block as first slot | width << 16.  Block (4 words): first slot |
+// width << 16, first stage, stages, 0; every slot of the role's array is in one block (no
+// stage: written 0), the blocks with most work first.  Stage (4 words): the staged block,
+// first path reference, paths, 0.  Unit (4 words): x1 block, output block, first path
+// reference, paths (<= kUvwzUnitPaths).  Records and references are 16-byte aligned.
+constexpr size_t kUvwzEntries = 2;
+constexpr int kUvwzHeader = 20;
+constexpr int kUvwzMaxD = 7;
+constexpr int kUvwzUnitPaths = 3;
+struct UvwzShape {
+    int nc1, nc2, nco, d1max, d2max, d3max, dmax, blocks[3], units;
+};
+// false where a block is wider than kUvwzMaxD
+bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
+                            std::vector<uint32_t>& out, UvwzShape* shape, const std::vector<double>* dense = nullptr);
+// whether the kernels' LDS tiles fit a CU
+bool uvwz_fits(const UvwzShape& s);
+// role 0: out from x1, x2; role 1: grad_x1 from grad_out, x2; weight of (p, a, v, o) at
+// p ps + a sa + v sv + o so.  Writes every element of out.
+hipError_t launch_uvwz_mix(const float* xa, const float* xb, const float* w, float* out, int64_t N, int A, int V, int O,
+                           int64_t sa, int64_t sv, int64_t so, int64_t ps, const UvwzShape& s, const uint32_t* table,
+                           int role, hipStream_t stream);
+hipError_t launch_uvwz_grad_x2(const float* x1, const float* g, const float* w, float* gx2, int64_t N, int U, int V,
+                               int W, const UvwzShape& s, const uint32_t* table, hipStream_t stream);
+hipError_t launch_uvwz_grad_w(const float* x1, const float* x2, const float* g, float* gw, int64_t N, int U, int V,
+                              int W, const UvwzShape& s, const uint32_t* table, hipStream_t stream);
+
 // Dense real tensor of the operation (see spingtp_dense_tensor_host), float64.
 void build_dense_tensor(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
                         std::vector<double>& T);
@@ -281,6 +318,8 @@ struct spingtp_plan_s {
     uint32_t* d_uvw;
     size_t uvw_off[3];
     int uvw_blocks[3], uvw_max_d3[3], uvw_paths;
+    uint32_t* d_uvwz;  // the block table of uvw_blocks.hip, nullptr where a block is too wide
+    spingtp::UvwzShape uvwz;
     // mixed degrees on the large-degree kernel of the largest degree: d_aux holds the
     // degree triples of the forward, the grad_x1 and the grad_x2 launches
     bool padded;

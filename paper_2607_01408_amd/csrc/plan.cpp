@@ -862,6 +862,150 @@ void weight_paths(int L1, int L2, int LO, const int* spins, int n_spins, const s
             }
 }
 
+bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
+                            std::vector<uint32_t>& out, UvwzShape* shape, const std::vector<double>* dense) {
+    if (2 * std::max(L1, std::max(L2, LO)) + 1 > kUvwzMaxD) return false;
+    std::vector<double> own;
+    if (dense == nullptr) build_dense_tensor(L1, L2, LO, spins, n_spins, flags, own);
+    const std::vector<double>& T = dense != nullptr ? *dense : own;
+    std::vector<std::array<int, 3>> paths;
+    tensor_paths(L1, L2, LO, spins, n_spins, T, paths);
+    const int degree[3] = {L1, L2, LO};
+    int widths[3];
+    // block b = i (L + 1) + l of an axis: slots i (L + 1)^2 + l^2 .. + 2 l
+    auto first = [&](int ax, int b) {
+        const int n = degree[ax] + 1, i = b / n, l = b - i * n;
+        return i * n * n + l * l;
+    };
+    auto width = [&](int ax, int b) { return 2 * (b % (degree[ax] + 1)) + 1; };
+    auto packed = [&](int ax, int b) {
+        return static_cast<uint32_t>(first(ax, b)) | (static_cast<uint32_t>(width(ax, b)) << 16);
+    };
+    for (int ax = 0; ax < 3; ++ax) widths[ax] = n_spins * (degree[ax] + 1) * (degree[ax] + 1);
+    auto value = [&](int k1, int k2, int k3) {
+        const double v = T[(static_cast<size_t>(k1) * widths[1] + k2) * widths[2] + k3];
+        return std::fabs(v) <= 1e-12 ? 0.0 : v;  // quadrature round-off of an exact zero
+    };
+    const int np = static_cast<int>(paths.size());
+    UvwzShape& s = *shape;
+    s = UvwzShape{};
+    s.nc1 = widths[0];
+    s.nc2 = widths[1];
+    s.nco = widths[2];
+    s.d1max = 2 * L1 + 1;
+    s.d2max = 2 * L2 + 1;
+    s.d3max = 2 * LO + 1;
+    s.dmax = std::max(s.d1max, std::max(s.d2max, s.d3max));
+    // entries of every (path, k1, k3) and the dense values of every path
+    std::vector<std::vector<std::vector<std::pair<uint32_t, float>>>> ent(np);
+    std::vector<std::vector<float>> full(np);
+    for (int p = 0; p < np; ++p) {
+        const int f1 = first(0, paths[p][0]), f2 = first(1, paths[p][1]), f3 = first(2, paths[p][2]);
+        const int d1 = width(0, paths[p][0]), d2 = width(1, paths[p][1]), d3 = width(2, paths[p][2]);
+        for (int k1 = 0; k1 < d1; ++k1)
+            for (int k3 = 0; k3 < d3; ++k3) {
+                ent[p].emplace_back();
+                for (int k2 = 0; k2 < d2; ++k2) {
+                    const float v = static_cast<float>(value(f1 + k1, f2 + k2, f3 + k3));
+                    full[p].push_back(v);
+                    if (v != 0.f) ent[p].back().push_back({static_cast<uint32_t>(f2 + k2), v});
+                }
+                if (ent[p].back().size() > kUvwzEntries) return false;  // the real bases couple at most two
+            }
+    }
+    out.assign(kUvwzHeader, 0u);
+    auto put_float = [&](float v) {
+        uint32_t w = 0;
+        std::memcpy(&w, &v, 4);
+        out.push_back(w);
+    };
+    out[0] = static_cast<uint32_t>(np);
+    // a reference to path p: its index, its entry records, its dense values, its output block
+    std::vector<std::array<uint32_t, 4>> ref(np);
+    for (int p = 0; p < np; ++p) {
+        ref[p] = {static_cast<uint32_t>(p), static_cast<uint32_t>(out.size()), 0u, packed(2, paths[p][2])};
+        for (const auto& list : ent[p])
+            for (size_t t = 0; t < kUvwzEntries; ++t) {
+                const bool live = t < list.size();
+                out.push_back(live ? list[t].first : static_cast<uint32_t>(s.nc2));
+                put_float(live ? list[t].second : 0.f);
+            }
+    }
+    for (int p = 0; p < np; ++p) {
+        ref[p][2] = static_cast<uint32_t>(out.size());
+        for (const float v : full[p]) put_float(v);
+    }
+    auto align4 = [&] { out.resize((out.size() + 3) / 4 * 4, 0u); };
+    align4();
+    // role: its output axis, the axis of the staged blocks, the axis whose width counts the work
+    const int ax_out[3] = {2, 0, 1}, ax_in[3] = {0, 2, 0}, ax_work[3] = {0, 2, 2};
+    for (int role = 0; role < 3; ++role) {
+        struct Block {
+            int b = 0, work = 0;
+            std::map<int, std::vector<int>> stages;
+        };
+        std::vector<Block> blocks(static_cast<size_t>(n_spins) * (degree[ax_out[role]] + 1));
+        for (size_t b = 0; b < blocks.size(); ++b) blocks[b].b = static_cast<int>(b);
+        for (int p = 0; p < np; ++p) {
+            Block& k = blocks[paths[p][ax_out[role]]];
+            k.stages[paths[p][ax_in[role]]].push_back(p);
+            k.work += width(ax_work[role], paths[p][ax_work[role]]);
+        }
+        std::stable_sort(blocks.begin(), blocks.end(), [](const Block& a, const Block& b) { return a.work > b.work; });
+        std::vector<uint32_t> bw, sw, rw;
+        for (const Block& k : blocks) {
+            const uint32_t head[4] = {packed(ax_out[role], k.b), static_cast<uint32_t>(sw.size() / 4),
+                                      static_cast<uint32_t>(k.stages.size()), 0u};
+            bw.insert(bw.end(), head, head + 4);
+            for (const auto& st : k.stages) {
+                const uint32_t w[4] = {packed(ax_in[role], st.first), static_cast<uint32_t>(rw.size() / 4),
+                                       static_cast<uint32_t>(st.second.size()), 0u};
+                sw.insert(sw.end(), w, w + 4);
+                for (const int p : st.second) rw.insert(rw.end(), ref[p].begin(), ref[p].end());
+            }
+        }
+        s.blocks[role] = static_cast<int>(blocks.size());
+        const std::vector<uint32_t>* parts[3] = {&bw, &sw, &rw};
+        const int at[3] = {3 + 4 * role, 5 + 4 * role, 6 + 4 * role};
+        out[4 + 4 * role] = static_cast<uint32_t>(blocks.size());
+        for (int i = 0; i < 3; ++i) {
+            out[at[i]] = static_cast<uint32_t>(out.size());
+            out.insert(out.end(), parts[i]->begin(), parts[i]->end());
+        }
+    }
+    // units of the weight gradient: the paths of each (x1 block, output block) pair in even
+    // groups of at most kUvwzUnitPaths, those with most work first
+    struct Unit {
+        int b1, b3;
+        std::vector<int> p;
+    };
+    std::map<std::pair<int, int>, std::vector<int>> pairs;
+    for (int p = 0; p < np; ++p) pairs[{paths[p][0], paths[p][2]}].push_back(p);
+    std::vector<Unit> units;
+    for (const auto& pr : pairs) {
+        const size_t n = pr.second.size(), groups = (n + kUvwzUnitPaths - 1) / kUvwzUnitPaths;
+        for (size_t g = 0; g < groups; ++g)
+            units.push_back({pr.first.first, pr.first.second,
+                             std::vector<int>(pr.second.begin() + n * g / groups, pr.second.begin() + n * (g + 1) / groups)});
+    }
+    std::stable_sort(units.begin(), units.end(), [&](const Unit& a, const Unit& b) {
+        return width(2, a.b3) * a.p.size() > width(2, b.b3) * b.p.size();
+    });
+    s.units = static_cast<int>(units.size());
+    out[15] = static_cast<uint32_t>(out.size());
+    out[16] = static_cast<uint32_t>(units.size());
+    uint32_t next = 0;
+    for (const Unit& u : units) {
+        const uint32_t w[4] = {packed(0, u.b1), packed(2, u.b3), next, static_cast<uint32_t>(u.p.size())};
+        out.insert(out.end(), w, w + 4);
+        next += static_cast<uint32_t>(u.p.size());
+    }
+    out[17] = static_cast<uint32_t>(out.size());
+    for (const Unit& u : units)
+        for (const int p : u.p) out.insert(out.end(), ref[p].begin(), ref[p].end());
+    return true;
+}
+
 bool build_uvw_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
                      std::vector<uint32_t>& out, const std::vector<double>* dense, int role) {
     std::vector<double> own;
@@ -1263,10 +1407,11 @@ struct PlanHost {
     int spin_mode = 0, dir_lds = 0;
     const spingtp::KernelEntry *k = nullptr, *kd = nullptr, *kv1 = nullptr, *kw = nullptr;
     std::vector<double> tab, tab_bwd;
-    std::vector<uint32_t> aux, pre, pre_bwd, dir, dir_b1, dir_b2, pre_w, bw1w, uvw;
+    std::vector<uint32_t> aux, pre, pre_bwd, dir, dir_b1, dir_b2, pre_w, bw1w, uvw, uvwz;
     size_t uvw_off[3] = {0, 0, 0};  // first word of each role's table in uvw
     bool padded = false;            // mixed degrees on the large-degree kernel (aux: 3 degree triples)
     spingtp::Bw1wShape bw1w_shape{};
+    spingtp::UvwzShape uvwz_shape{};
     bool has_backward = false, same_bwd = false;
 };
 
@@ -1405,14 +1550,17 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
         if (k != nullptr && k->family == 4) spingtp::build_mfma_operands(L1, aux);
         if (flags & SPINGTP_FULLY_CONNECTED) {
             // the forward's table, then those of the gradients w.r.t. x1 and x2, in one buffer
+            if (dense.empty()) spingtp::build_dense_tensor(L1, L2, Lout, spins, n_spins, basis, dense);
             for (int role = 0; role < 3; ++role) {
                 std::vector<uint32_t> t;
-                if (!spingtp::build_uvw_table(L1, L2, Lout, spins, n_spins, basis, t, dense.empty() ? nullptr : &dense,
-                                              role))
+                if (!spingtp::build_uvw_table(L1, L2, Lout, spins, n_spins, basis, t, &dense, role))
                     return SPINGTP_ERR_UNSUPPORTED;
                 h.uvw_off[role] = h.uvw.size();
                 h.uvw.insert(h.uvw.end(), t.begin(), t.end());
             }
+            if (!spingtp::build_uvw_blocks_table(L1, L2, Lout, spins, n_spins, basis, h.uvwz, &h.uvwz_shape, &dense) ||
+                !spingtp::uvwz_fits(h.uvwz_shape))
+                h.uvwz.clear();
         }
         if (kv1->family == 5 &&
             !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre, false, weighted ? &dense : nullptr))
@@ -1445,7 +1593,7 @@ struct DeviceApi {
 struct PlanDevice {
     float *tab = nullptr, *tab_bwd = nullptr;
     uint32_t *aux = nullptr, *pre = nullptr, *pre_bwd = nullptr, *dir = nullptr, *dir_b1 = nullptr,
-             *dir_b2 = nullptr, *pre_w = nullptr, *bw1w = nullptr, *uvw = nullptr;
+             *dir_b2 = nullptr, *pre_w = nullptr, *bw1w = nullptr, *uvw = nullptr, *uvwz = nullptr;
 };
 
 // Uploads every non-empty table (fp32 tables rounded to nearest).  On any failure every
@@ -1477,7 +1625,8 @@ spingtp_status upload_plan(const PlanHost& h, const DeviceApi& api, PlanDevice& 
     }
     const std::pair<const std::vector<uint32_t>*, uint32_t**> words[] = {
         {&h.aux, &d.aux}, {&h.pre, &d.pre}, {&h.pre_bwd, &d.pre_bwd}, {&h.dir, &d.dir}, {&h.dir_b1, &d.dir_b1},
-        {&h.dir_b2, &d.dir_b2}, {&h.pre_w, &d.pre_w}, {&h.bw1w, &d.bw1w}, {&h.uvw, &d.uvw}};
+        {&h.dir_b2, &d.dir_b2}, {&h.pre_w, &d.pre_w}, {&h.bw1w, &d.bw1w}, {&h.uvw, &d.uvw},
+        {&h.uvwz, &d.uvwz}};
     for (const auto& w : words)
         put(w.first->data(), w.first->size() * sizeof(uint32_t), reinterpret_cast<void**>(w.second));
     if (fail == 0) return SPINGTP_OK;
@@ -1517,7 +1666,7 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
         for (void* q : {static_cast<void*>(d.tab), static_cast<void*>(d.tab_bwd), static_cast<void*>(d.aux),
                         static_cast<void*>(d.pre), static_cast<void*>(d.pre_bwd), static_cast<void*>(d.dir),
                         static_cast<void*>(d.dir_b1), static_cast<void*>(d.dir_b2), static_cast<void*>(d.pre_w),
-                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw)})
+                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw), static_cast<void*>(d.uvwz)})
             if (q != nullptr) (void)hipFree(q);
         return SPINGTP_ERR_OUT_OF_MEMORY;
     }
@@ -1546,6 +1695,8 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
     p->d_bw1w = d.bw1w;
     p->bw1w = h.bw1w_shape;
     p->d_uvw = d.uvw;
+    p->d_uvwz = d.uvwz;
+    p->uvwz = h.uvwz_shape;
     for (int role = 0; role < 3; ++role) {
         const size_t o = h.uvw_off[role];
         p->uvw_off[role] = o;
@@ -1596,7 +1747,7 @@ extern "C" spingtp_status spingtp_plan_upload_selftest_host(int L1, int L2, int 
         for (void* q : {static_cast<void*>(d.tab), static_cast<void*>(d.tab_bwd), static_cast<void*>(d.aux),
                         static_cast<void*>(d.pre), static_cast<void*>(d.pre_bwd), static_cast<void*>(d.dir),
                         static_cast<void*>(d.dir_b1), static_cast<void*>(d.dir_b2), static_cast<void*>(d.pre_w),
-                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw)})
+                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw), static_cast<void*>(d.uvwz)})
             if (q != nullptr) api.release(api.ctx, q);
     return su;
 }
@@ -1659,6 +1810,7 @@ spingtp_status spingtp_plan_destroy(spingtp_plan plan) {
     release(plan->d_pre);
     release(plan->d_pre_bwd);
     release(plan->d_uvw);
+    release(plan->d_uvwz);
     if (plan->own_tab_bwd) release(plan->d_tab_bwd);
     if (switched) (void)hipSetDevice(cur);
     delete plan;

@@ -245,3 +245,20 @@ def test_uvw_backward_bitwise_deterministic():
     h1, h2, hw = plan.backward_fully_connected(x1, x2, w, gy)
     torch.cuda.synchronize()
     assert torch.equal(g1, h1) and torch.equal(g2, h2) and torch.equal(gw, hw)
+
+
+@pytest.mark.parametrize("L1,L2,LO,spins,N,U,V,W", [
+    (2, 2, 2, S3, 16, 64, 1, 64),    # whole tiles throughout
+    (2, 2, 2, S3, 17, 81, 1, 68),    # a ragged edge tile, a second 64-channel chunk with 17 channels
+    (1, 1, 2, S3, 5, 33, 2, 67),     # W not a multiple of 4 (4-byte weight loads), two v
+    (3, 3, 3, S3, 9, 20, 1, 12),     # blocks of 7 slots
+    (2, 2, 2, S5, 18, 6, 3, 18),     # five spins: invalid blocks of 3 slots, pairs with many paths
+    (2, 2, 2, S3, 20, 2, 40, 3),     # few channels, many v: the pairwise kernel for out, the others new
+    (0, 1, 1, S3, 33, 65, 1, 129),   # blocks of one slot
+])
+def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
+    """Edges of the block kernels' tiles (16 edges, 64 staged channels in halves of 32 and K
+    steps of 16, 64 output channels, 32 x 32 weight-gradient tiles) and both sides of their
+    dispatch, forward and the three gradients."""
+    run_uvw(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
+    run_uvw_backward(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
