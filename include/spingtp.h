@@ -71,7 +71,9 @@ typedef enum { SPINGTP_FP32 = 0, SPINGTP_BF16 = 1 } spingtp_dtype;
 #define SPINGTP_BASIS_PARITY 2u
 
 /* Kernel choice, OR-ed into the flags of spingtp_plan_create: use the fp32
- * vector-ALU kernels even where a matrix-core kernel is built (family 4 below).
+ * vector-ALU kernels even where a matrix-core kernel is built (family 4 below), and
+ * the entry-list form of the direct kernel (family 6) where the unrolled one is
+ * (spins {-2..2}, L1 = L2 = Lout <= 2; the same results bit for bit).
  * The other entry points accept and ignore it. */
 #define SPINGTP_KERNEL_VALU 0x100u
 

@@ -26,8 +26,21 @@ spingtp_status spingtp::run_forward(spingtp_plan plan, const spingtp::KernelEntr
     const uint32_t* aux =
         aux_override != nullptr ? aux_override
                                 : (k->family == 5 ? plan->d_pre : (k->family == 6 ? plan->d_dir : plan->d_aux));
+    // the direct kernel with one x2 row per unit: unrolled where built (the entry-list form
+    // takes an x2 row per edge and every other shape)
+    int unrolled_role = -1;
+    if (k->launch_lds != nullptr && plan->unrolled != nullptr && (!shared_x2 || C == 1)) {
+        const uint32_t* const tables[3] = {plan->d_dir, plan->d_dir_b1, plan->d_dir_b2};
+        for (int role = 0; role < 3; ++role)
+            if (aux != nullptr && aux == tables[role] && plan->unrolled_off[role] != 0) unrolled_role = role;
+    }
     const hipError_t e =
-        k->launch_lds != nullptr
+        unrolled_role >= 0
+            ? plan->unrolled->launch[unrolled_role](
+                  x1, x2, out, N * C, plan->dtype == SPINGTP_FP32 ? 0 : 1,
+                  reinterpret_cast<const float*>(aux + plan->unrolled_off[unrolled_role]),
+                  static_cast<hipStream_t>(stream))
+        : k->launch_lds != nullptr
             ? k->launch_lds(x1, x2, out, N * C, shared_x2 ? C : 1, aux, plan->dir_lds_floats,
                             static_cast<hipStream_t>(stream))
             : (bwd_launch ? k->launch_bwd : k->launch)(x1, x2, out, N * C, shared_x2 ? C : 1,

@@ -9,6 +9,7 @@
 
 #include "../../include/spingtp.h"
 #include "layout.h"
+#include "tensor_pattern.h"
 
 namespace spingtp {
 
@@ -68,6 +69,23 @@ const KernelEntry* find_direct_kernel(int lds_floats, int dtype);
 // it (built here otherwise).
 void build_direct_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags, int role,
                         std::vector<uint32_t>& out, int* lds_floats, const std::vector<double>* dense = nullptr);
+
+// The direct kernel unrolled over the tensor's entries (direct_unrolled.h), spins {-2..2} at
+// L1 = L2 = Lout = L <= 2: per role its entries in order and its launch, whose `val` holds one
+// fp32 value per entry (device).  nullptr where none is built.
+struct UnrolledKernel {
+    int n[3];
+    const pattern::Entry* entries[3];
+    hipError_t (*launch[3])(const void* a, const void* b, void* out, int64_t units, int dtype, const float* val,
+                            hipStream_t stream);
+};
+const UnrolledKernel* find_unrolled_paper(int L);
+const UnrolledKernel* find_unrolled_paired(int L);
+const UnrolledKernel* find_unrolled_parity(int L);
+// The values of the role's entries from the dense tensor, in the kernel's order; false where
+// the tensor has an entry that the kernel lacks.
+bool unrolled_values(const UnrolledKernel& k, int role, int n1, int n2, int n3, const std::vector<double>& T,
+                     std::vector<uint32_t>& words);
 
 // Finds the instantiation for (L1, L2, Lout, spin mode, dtype); nullptr if none.
 // find_kernel returns the vector-ALU kernels, find_mfma_kernel the matrix-core
@@ -312,6 +330,8 @@ struct spingtp_plan_s {
     uint32_t* d_dir_b1;  // direct-kernel tables of the gradients w.r.t. x1 and x2, nullptr unless
     uint32_t* d_dir_b2;  //   the gradients run on the direct kernel
     const spingtp::KernelEntry* kernel_dir;  // the direct kernel of d_dir_b1 and d_dir_b2
+    const spingtp::UnrolledKernel* unrolled;  // its unrolled form, nullptr if none; per role the
+    size_t unrolled_off[3];                   //   first word of its values in d_dir, d_dir_b1, d_dir_b2 (0: none)
     int dir_lds_floats;  // LDS of the direct kernel's tiles (the same for its three tables)
     // entry tables of the fully connected product (SPINGTP_FULLY_CONNECTED, else nullptr):
     // roles 0 (forward), 1 and 2 (gradients w.r.t. x1 and x2), each from word uvw_off[role]

@@ -862,6 +862,24 @@ void weight_paths(int L1, int L2, int LO, const int* spins, int n_spins, const s
             }
 }
 
+bool unrolled_values(const UnrolledKernel& k, int role, int n1, int n2, int n3, const std::vector<double>& T,
+                     std::vector<uint32_t>& words) {
+    size_t nonzero = 0, live = 0;
+    for (const double v : T) nonzero += std::fabs(v) > 1e-12 ? 1 : 0;  // (quadrature round-off of exact zeros)
+    for (int i = 0; i < k.n[role]; ++i) {
+        const pattern::Entry& e = k.entries[role][i];
+        const int k1 = role == 0 ? e.a : (role == 1 ? e.o : e.b), k2 = role == 2 ? e.o : e.b, k3 = role == 0 ? e.o : e.a;
+        if (k1 >= n1 || k2 >= n2 || k3 >= n3) return false;
+        const double t = T[(static_cast<size_t>(k1) * n2 + k2) * n3 + k3];
+        const float v = std::fabs(t) > 1e-12 ? static_cast<float>(t) : 0.f;
+        live += v != 0.f ? 1 : 0;
+        uint32_t w = 0;
+        std::memcpy(&w, &v, 4);
+        words.push_back(w);
+    }
+    return live == nonzero;
+}
+
 bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
                             std::vector<uint32_t>& out, UvwzShape* shape, const std::vector<double>* dense) {
     if (2 * std::max(L1, std::max(L2, LO)) + 1 > kUvwzMaxD) return false;
@@ -1412,6 +1430,8 @@ struct PlanHost {
     bool padded = false;            // mixed degrees on the large-degree kernel (aux: 3 degree triples)
     spingtp::Bw1wShape bw1w_shape{};
     spingtp::UvwzShape uvwz_shape{};
+    const spingtp::UnrolledKernel* unrolled = nullptr;
+    size_t unrolled_off[3] = {0, 0, 0};
     bool has_backward = false, same_bwd = false;
 };
 
@@ -1546,6 +1566,28 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
         if (kd != nullptr && !fourier_bwd) {
             spingtp::build_direct_table(L1, L2, Lout, spins, n_spins, basis, 1, dir_b1, &lds_floats, &dense);
             spingtp::build_direct_table(L1, L2, Lout, spins, n_spins, basis, 2, dir_b2, &lds_floats, &dense);
+        }
+        // spins {-2..2} at one degree <= 2: the direct kernel unrolled over the tensor's entries,
+        // its values after each role's entry table.  Always the faster one there (12.8 M units,
+        // L = 2, fp32, paper basis: 4.58 -> 1.22 ms); larger degrees exceed the registers of a lane.
+        // SPINGTP_KERNEL_VALU keeps the entry-list kernel.
+        if (spin_mode == 2 && L1 == L2 && L2 == Lout && !dense.empty() && (flags & SPINGTP_KERNEL_VALU) == 0) {
+            const spingtp::UnrolledKernel* un = basis == SPINGTP_BASIS_REAL_PAPER ? spingtp::find_unrolled_paper(L1)
+                                                : basis == SPINGTP_BASIS_PARITY   ? spingtp::find_unrolled_parity(L1)
+                                                                                  : spingtp::find_unrolled_paired(L1);
+            std::vector<uint32_t>* const tables[3] = {&dir, &dir_b1, &dir_b2};
+            for (int role = 0; un != nullptr && role < 3; ++role) {
+                if (tables[role]->empty()) continue;
+                const size_t at = (tables[role]->size() + 15) / 16 * 16;  // a cache line of values starts each list
+                std::vector<uint32_t> words;
+                const int n = n_spins * (L1 + 1) * (L1 + 1);
+                if (!spingtp::unrolled_values(*un, role, n, n, n, dense, words)) continue;
+                tables[role]->resize(at, 0u);
+                tables[role]->insert(tables[role]->end(), words.begin(), words.end());
+                tables[role]->resize(tables[role]->size() + 32, 0u);
+                h.unrolled = un;
+                h.unrolled_off[role] = at;
+            }
         }
         if (k != nullptr && k->family == 4) spingtp::build_mfma_operands(L1, aux);
         if (flags & SPINGTP_FULLY_CONNECTED) {
@@ -1689,6 +1731,8 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
     p->d_dir_b1 = d.dir_b1;
     p->d_dir_b2 = d.dir_b2;
     p->kernel_dir = d.dir_b1 != nullptr ? h.kd : nullptr;
+    p->unrolled = h.unrolled;
+    for (int role = 0; role < 3; ++role) p->unrolled_off[role] = h.unrolled_off[role];
     p->dir_lds_floats = h.dir_lds;
     p->d_pre_w = d.pre_w;
     p->kernel_v1w = d.pre_w != nullptr ? h.kw : nullptr;

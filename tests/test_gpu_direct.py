@@ -22,7 +22,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("no GPU visible", allow_module_level=True)
 
-from paper_2607_01408_amd import Plan, SpinGTPError, workloads  # noqa: E402
+from paper_2607_01408_amd import Plan, SpinGTPError, paths_host, workloads  # noqa: E402
 
 S5 = (-2, -1, 0, 1, 2)
 S3 = (-1, 0, 1)
@@ -239,3 +239,29 @@ def test_chiral_workload_full_size_sampled():
     err = rel_l2(g, ref)
     print(f"[direct] chiral full size sampled rel_l2={err:.3e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2])
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_unrolled_against_entry_lists(L, basis, dtype):
+    """The unrolled kernel (spins {-2..2}, degree <= 2) against the entry-list kernel
+    (valu_only) on the same inputs: one unit, around a wave's 64 and a workgroup's 256, and
+    path-weighted plans (whose tensor is not symmetric in the inputs), forward and gradients.
+    Both sum the same fp32 products in another order: a sum of at most 100 terms is within
+    100 x 2^-24 of the largest partial sum (1e-5 of the result's norm), then one rounding of
+    the bf16 output."""
+    n_paths = len(paths_host(L, L, L, S5, basis))
+    rng = np.random.default_rng(L + basis)
+    for weights in (None, rng.standard_normal(n_paths)):
+        fast = Plan(L, L, L, S5, dtype, basis, weights=weights)
+        slow = Plan(L, L, L, S5, dtype, basis, weights=weights, valu_only=True)
+        for units in (1, 63, 64, 65, 255, 257, 1000):
+            x1, x2, g = (workloads.draw(L, units, 1, 7000 + i + units, dtype, S5, "unit", "cuda") for i in range(3))
+            pairs = [(fast.forward(x1, x2), slow.forward(x1, x2))]
+            pairs += list(zip(fast.backward(x1, x2, g), slow.backward(x1, x2, g)))
+            for a, b in pairs:
+                a, b = a.double(), b.double()
+                rel = float((a - b).norm() / b.norm())
+                assert rel <= (1e-5 if dtype == "fp32" else 2.0 ** -8), (units, rel)
+                assert float(a.reshape(units, -1)[:, torch.as_tensor(~valid_mask(S5, L), device="cuda")].abs().max()) == 0
