@@ -59,6 +59,20 @@ extern "C" spingtp_status spingtp_forward_v1(spingtp_plan plan, const void* x1, 
     return spingtp::run_forward(plan, plan ? plan->kernel_v1 : nullptr, x1, x2, out, N, C, true, stream);
 }
 
+namespace {
+
+// The shared-x2 weighted forward on the block kernels (channel_blocks.hip) with nv
+// second-input channels per launch.  Their cost per edge has a fixed part (K, two barriers, the
+// rows) that tensors of a few dozen entries do not earn back: 64 channels, 1,024 edges, us,
+// entry lists against blocks: 88 entries 10 / 14, 353 17 / 15, 683 27 / 18, 1,043 50 / 23,
+// 2,003 148 / 50.
+bool use_blocks(spingtp_plan plan, int nv) {
+    return plan->d_cw != nullptr && plan->cw.nnz >= 256 &&
+           spingtp::cw_fwd_lds_floats(plan->cw, nv) <= spingtp::kBw1wMaxLdsFloats;
+}
+
+}  // namespace
+
 extern "C" spingtp_status spingtp_forward_v1_weighted(spingtp_plan plan, const void* x1, const void* x2,
                                                       const float* weights, void* out, int64_t N, int64_t C,
                                                       void* stream) {
@@ -79,8 +93,12 @@ extern "C" spingtp_status spingtp_forward_v1_weighted(spingtp_plan plan, const v
         int cur = -1;
         if (hipGetDevice(&cur) != hipSuccess) return SPINGTP_ERR_HIP;
         if (cur != plan->device) return SPINGTP_ERR_INVALID_ARG;
-        const hipError_t e = spingtp::launch_fwd_cw(plan->dtype == SPINGTP_FP32 ? 0 : 1, true, x1, x2, weights, out,
-                                                    N, C, plan->bw1w, plan->d_bw1w, static_cast<hipStream_t>(stream));
+        const int dt = plan->dtype == SPINGTP_FP32 ? 0 : 1;
+        const hipStream_t st = static_cast<hipStream_t>(stream);
+        const hipError_t e =
+            use_blocks(plan, 1)
+                ? spingtp::launch_cw_fwd(dt, x1, x2, weights, out, N, C, plan->cw, plan->d_cw, st, 0, false, 1, 0, 0)
+                : spingtp::launch_fwd_cw(dt, true, x1, x2, weights, out, N, C, plan->bw1w, plan->d_bw1w, st);
         return e == hipSuccess ? SPINGTP_OK : SPINGTP_ERR_HIP;
     }
     // the weighted precontracted kernel takes the weights in place of the plan tables
@@ -120,7 +138,8 @@ extern "C" spingtp_status spingtp_backward_v1_weighted(spingtp_plan plan, const 
     if (cur != plan->device) return SPINGTP_ERR_INVALID_ARG;
     const hipError_t e = spingtp::launch_bwd_v1w(
         plan->dtype == SPINGTP_FP32 ? 0 : 1, true, x1, x2, weights, grad_out, grad_x1, grad_x2, grad_weights,
-        static_cast<float*>(workspace), N, C, plan->bw1w, plan->d_bw1w, static_cast<hipStream_t>(stream));
+        static_cast<float*>(workspace), N, C, plan->bw1w, plan->d_bw1w, static_cast<hipStream_t>(stream), 0, false,
+        plan->d_cw != nullptr ? &plan->cw : nullptr, plan->d_cw);
     return e == hipSuccess ? SPINGTP_OK : SPINGTP_ERR_HIP;
 }
 
@@ -197,18 +216,23 @@ extern "C" spingtp_status spingtp_forward_depthwise(spingtp_plan plan, const voi
     // up to kFwdCwMaxNv channels per launch, as many as the LDS holds without fewer
     // workgroups per CU than one channel gets (at least two); later launches add
     // into out, in channel order
-    const int lds1 = spingtp::fwd_cw_lds_floats(plan->bw1w, 1);
-    const int per_cu1 = std::min(2, spingtp::kBw1wMaxLdsFloats / std::max(lds1, 1));
+    const bool blocks = use_blocks(plan, 1);
+    auto lds = [&](int nv) {
+        return blocks ? spingtp::cw_fwd_lds_floats(plan->cw, nv) : spingtp::fwd_cw_lds_floats(plan->bw1w, nv);
+    };
+    const int per_cu1 = std::min(2, spingtp::kBw1wMaxLdsFloats / std::max(lds(1), 1));
     int nv_max = 1;
-    while (nv_max < spingtp::kFwdCwMaxNv &&
-           spingtp::kBw1wMaxLdsFloats / spingtp::fwd_cw_lds_floats(plan->bw1w, nv_max + 1) >= per_cu1)
-        ++nv_max;
+    while (nv_max < spingtp::kFwdCwMaxNv && spingtp::kBw1wMaxLdsFloats / lds(nv_max + 1) >= per_cu1) ++nv_max;
+    const int dt = plan->dtype == SPINGTP_FP32 ? 0 : 1;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
     for (int64_t v = 0; v < V;) {
         const int nv = static_cast<int>(std::min<int64_t>(nv_max, V - v));
-        const hipError_t e = spingtp::launch_fwd_cw(
-            plan->dtype == SPINGTP_FP32 ? 0 : 1, true, x1, static_cast<const char*>(x2) + v * n2 * elem,
-            weights + v * wslice, out, N, C, plan->bw1w, plan->d_bw1w, static_cast<hipStream_t>(stream), V * n2,
-            v > 0, nv, n2, wslice);
+        const void* xv = static_cast<const char*>(x2) + v * n2 * elem;
+        const hipError_t e =
+            blocks ? spingtp::launch_cw_fwd(dt, x1, xv, weights + v * wslice, out, N, C, plan->cw, plan->d_cw, st,
+                                            V * n2, v > 0, nv, n2, wslice)
+                   : spingtp::launch_fwd_cw(dt, true, x1, xv, weights + v * wslice, out, N, C, plan->bw1w,
+                                            plan->d_bw1w, st, V * n2, v > 0, nv, n2, wslice);
         if (e != hipSuccess) return SPINGTP_ERR_HIP;
         v += nv;
     }
@@ -250,7 +274,7 @@ extern "C" spingtp_status spingtp_backward_depthwise(spingtp_plan plan, const vo
             plan->dtype == SPINGTP_FP32 ? 0 : 1, true, x1, static_cast<const char*>(x2) + v * n2 * elem,
             weights + v * wslice, grad_out, grad_x1, static_cast<char*>(grad_x2) + v * n2 * elem,
             grad_weights + v * wslice, static_cast<float*>(workspace), N, C, plan->bw1w, plan->d_bw1w,
-            static_cast<hipStream_t>(stream), V * n2, v > 0);
+            static_cast<hipStream_t>(stream), V * n2, v > 0, plan->d_cw != nullptr ? &plan->cw : nullptr, plan->d_cw);
         if (e != hipSuccess) return SPINGTP_ERR_HIP;
     }
     return SPINGTP_OK;

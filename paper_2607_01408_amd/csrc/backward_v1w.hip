@@ -48,6 +48,7 @@
 //   list ends with 96 more of those (the prefetch of the last blocks reads them).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 
@@ -395,13 +396,23 @@ hipError_t raise_lds_limit(const void* kernel) {
 template <typename TIO, bool SHARED>
 hipError_t launch_typed(const void* x1, const void* x2, const float* w, const void* g, void* gx1, void* gx2,
                         float* gw, float* ws, int64_t N, int64_t C, const Bw1wShape& s, const uint32_t* tab,
-                        hipStream_t stream, int64_t x2s, bool acc_gx1) {
+                        hipStream_t stream, int64_t x2s, bool acc_gx1, const CwShape* cw, const uint32_t* cw_tab) {
     const int64_t tiles = (C + kBw1wLanes - 1) / kBw1wLanes;
     int64_t groups = 0, epg = 0;
-    bw1w_groups(N, C, &groups, &epg, bw_target_groups(SHARED ? s.lds_floats : s.lds_unit_bwd));
+    int target = bw_target_groups(SHARED ? s.lds_floats : s.lds_unit_bwd);
+    // the block kernels where their LDS fits (faster at every shape measured: 88 entries, 1,024
+    // edges 44 -> 33 us; 2,048 edges of 683 entries 186 -> 85), with as many workgroups as are resident at once
+    // (never more edge ranges than the workspace is sized for)
+    const bool blocks_kernel = SHARED && cw != nullptr && cw_tab != nullptr && cw_bwd_lds_floats(*cw) <= kBw1wMaxLdsFloats;
+    if (blocks_kernel) target = std::min(target, 256 * std::min(2, kBw1wMaxLdsFloats / cw_bwd_lds_floats(*cw)));
+    bw1w_groups(N, C, &groups, &epg, target);
     float* ws_x2 = ws;
     float* ws_w = SHARED ? ws + tiles * N * s.nc2 : ws;
-    if (groups > 0 && tiles > 0) {
+    if (blocks_kernel && groups > 0 && tiles > 0) {
+        const hipError_t e = launch_cw_bwd(sizeof(TIO) == 4 ? 0 : 1, x1, x2, w, g, gx1, gx2, ws_x2, ws_w, N, C, groups,
+                                           epg, *cw, cw_tab, stream, x2s, acc_gx1);
+        if (e != hipSuccess) return e;
+    } else if (groups > 0 && tiles > 0) {
         if (groups > 0x7fffffff || tiles > 0xffff) return hipErrorInvalidValue;
         const int lds_floats = SHARED ? s.lds_floats : s.lds_unit_bwd;
         const size_t bytes = static_cast<size_t>(lds_floats) * sizeof(float);
@@ -418,7 +429,8 @@ hipError_t launch_typed(const void* x1, const void* x2, const float* w, const vo
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const int64_t nx2 = SHARED ? N * s.nc2 : 0;  // per-unit gx2 is written by the kernel
+    // per-unit gx2 is written by the kernel, and so is that of a single tile by the block kernel
+    const int64_t nx2 = SHARED && !(blocks_kernel && tiles == 1 && groups > 0) ? N * s.nc2 : 0;
     if (nx2 > 0) {
         const int64_t blocks = (nx2 + 255) / 256;
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
@@ -468,7 +480,8 @@ size_t bwcw_workspace_floats(int64_t N, int64_t C, const Bw1wShape& s) {
 
 hipError_t launch_bwd_v1w(int dtype, bool shared_x2, const void* x1, const void* x2, const float* w, const void* g,
                           void* gx1, void* gx2, float* gw, float* ws, int64_t N, int64_t C, const Bw1wShape& s,
-                          const uint32_t* tab, hipStream_t stream, int64_t x2_stride, bool accumulate_gx1) {
+                          const uint32_t* tab, hipStream_t stream, int64_t x2_stride, bool accumulate_gx1,
+                          const CwShape* cw, const uint32_t* cw_tab) {
     const int64_t x2s = x2_stride > 0 ? x2_stride : s.nc2;
     // the kernel carves its LDS from the table's sizes
     const int base = kBw1wLanes * (2 * bw_stride(s.np) + bw_stride(s.nc1) + bw_stride(s.nco));
@@ -476,17 +489,19 @@ hipError_t launch_bwd_v1w(int dtype, bool shared_x2, const void* x1, const void*
         if (s.lds_floats <= 0 || s.lds_floats > kBw1wMaxLdsFloats || s.lds_floats != base + bw_stride(s.nc2))
             return hipErrorInvalidValue;
         return dtype == 0
-                   ? launch_typed<float, true>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s, accumulate_gx1)
+                   ? launch_typed<float, true>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s, accumulate_gx1, cw,
+                                               cw_tab)
                    : launch_typed<uint16_t, true>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s,
-                                                  accumulate_gx1);
+                                                  accumulate_gx1, cw, cw_tab);
     }
     if (s.lds_unit_bwd <= 0 || s.lds_unit_bwd > kBw1wMaxLdsFloats ||
         s.lds_unit_bwd != base + 2 * kBw1wLanes * bw_stride(s.nc2))
         return hipErrorInvalidValue;
     return dtype == 0
-               ? launch_typed<float, false>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s, accumulate_gx1)
+               ? launch_typed<float, false>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s, accumulate_gx1,
+                                                nullptr, nullptr)
                : launch_typed<uint16_t, false>(x1, x2, w, g, gx1, gx2, gw, ws, N, C, s, tab, stream, x2s,
-                                               accumulate_gx1);
+                                               accumulate_gx1, nullptr, nullptr);
 }
 
 template <typename TIO, bool SHARED, int NV>

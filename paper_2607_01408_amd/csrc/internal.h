@@ -137,7 +137,8 @@ const KernelEntry* find_pre_kernel_large(int ks, int nt, int dtype);
 // number of path slots, written to *n_rows; false otherwise).  One block of rows.
 // The path slots follow the items: x1 slot | path << 16.
 bool build_pre_tables_channel_weighted(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
-                                       int ks, std::vector<uint32_t>& out, int* n_rows);
+                                       int ks, std::vector<uint32_t>& out, int* n_rows,
+                                       const std::vector<double>* dense = nullptr);
 std::vector<int> slot_blocks(int L, const int* spins, int n_spins);
 // dense: the tensor to tabulate (the plan's, e.g. path-weighted); built here when nullptr.
 bool build_pre_tables(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
@@ -200,13 +201,15 @@ size_t bwcw_workspace_floats(int64_t N, int64_t C, const Bw1wShape& s);
 // dtype 0: fp32 x1, x2, grad_out, gx1, gx2; 1: bf16.  Weights and gW are fp32.
 // shared_x2: x2 [N][NC2] shared by the channels (spingtp_backward_v1_weighted), else
 // x2 [N][C][NC2] per unit (spingtp_backward_weighted).
+// cw, cw_tab (shared x2): the block kernels' table; nullptr runs the entry lists.
 // x2_stride (shared x2): elements between the x2 (and gx2) rows of consecutive edges,
 // 0 for NC2; accumulate_gx1: add gx1 to what grad_x1 holds (the depthwise mode's sum
 // over its second-input channels).
+struct CwShape;
 hipError_t launch_bwd_v1w(int dtype, bool shared_x2, const void* x1, const void* x2, const float* w, const void* g,
                           void* gx1, void* gx2, float* gw, float* ws, int64_t N, int64_t C, const Bw1wShape& s,
                           const uint32_t* tab, hipStream_t stream, int64_t x2_stride = 0,
-                          bool accumulate_gx1 = false);
+                          bool accumulate_gx1 = false, const CwShape* cw = nullptr, const uint32_t* cw_tab = nullptr);
 // out[n][c] = sum_p W[c][p] T_p(x1[n][c], x2[n][c]) (spingtp_forward_weighted), or with
 // x2[n] shared by the channels (shared_x2, spingtp_forward_v1_weighted).
 // x2_stride, accumulate: as for launch_bwd_v1w (accumulate adds to out).
@@ -219,6 +222,41 @@ hipError_t launch_fwd_cw(int dtype, bool shared_x2, const void* x1, const void* 
                          int64_t x2_stride = 0, bool accumulate = false, int nv = 1, int64_t x2v = 0,
                          int64_t wslice = 0);
 int fwd_cw_lds_floats(const Bw1wShape& s, int nv);
+
+// The shared-x2 forms of that product and its gradients for blocks up to kCwMaxD wide
+// (channel_blocks.hip).  Table words: header [kCwHeader]: [0] n_paths, [1] NC1, [2] NC2, [3] NCO,
+// [4] and [5] the parts (1 or 2) of the forward's and the gradients' blocks; word offsets: for the forward (output blocks) [8] schedule (kCwFwdWaves + 1 block numbers),
+// [9] blocks, [10] references, [11] items; for the gradients (x1 blocks) [12..15] the same with
+// bwd_waves; [16] tile rows, [17] tile columns, [18] segments, [19] entries of grad_x2;
+// [20] number of tiles, [21] schedule of the tiles (bwd_waves + 1).
+// Block (8 words): first slot | width << 16, first reference, references (at most 64, by
+// contracted width), first item, items, the references of width 1, 3, 5, 7 (a byte each), its
+// part, 0: the paths of a large block may be split over two waves, whose sums are added as the
+// rows are stored.  Reference (4 words): path, the contracted block's first slot, offset
+// of the path's K ([contracted slot][output slot], row stride 1, 4 or 8 by width) in the
+// wave's region, 0.  Item (4 words): two x2 slots (low and high half), two values, the K
+// element they make.  Tile: 16 rows path | x1 slot << 16 (padding: n_paths, NC1: the zero
+// columns) and its first output slot, the first slot of a spin's blocks.  Segments: NC2 + 1
+// entry numbers; an entry: index of an M element (tile 256 + row 16 + column), value.
+constexpr int kCwHeader = 24;
+constexpr int kCwMaxD = 7;
+constexpr int kCwFwdWaves = 8;
+struct CwShape {
+    int np, nc1, nc2, nco, kfloats[2], parts[2], tiles, dmax, bwd_waves, nnz;
+};
+// bwd_waves: 8 or 16, the waves of the gradients' workgroups.
+bool build_cw_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags, int bwd_waves,
+                    std::vector<uint32_t>& out, CwShape* shape, const std::vector<double>* dense = nullptr);
+int cw_fwd_lds_floats(const CwShape& s, int nv);
+int cw_bwd_lds_floats(const CwShape& s);
+hipError_t launch_cw_fwd(int dtype, const void* x1, const void* x2, const float* w, void* out, int64_t N, int64_t C,
+                         const CwShape& s, const uint32_t* tab, hipStream_t stream, int64_t x2s, bool add, int nv,
+                         int64_t x2v, int64_t wslice);
+// groups x epg: the edge ranges (bw1w_groups); ws_x2: partial gx2 per channel tile (unused with
+// one tile, which writes gx2), ws_w: partial gW per edge range.
+hipError_t launch_cw_bwd(int dtype, const void* x1, const void* x2, const float* w, const void* g, void* gx1, void* gx2,
+                         float* ws_x2, float* ws_w, int64_t N, int64_t C, int64_t groups, int64_t epg, const CwShape& s,
+                         const uint32_t* tab, hipStream_t stream, int64_t x2s, bool add);
 
 // Paths of the instruction-weighted product (spingtp_paths_host): the block triples
 // (i (L+1) + l of spin index i and degree l, per input and output) on which T has
@@ -324,6 +362,8 @@ struct spingtp_plan_s {
     const spingtp::KernelEntry* kernel_v1w;  // its kernel (spingtp_forward_v1_weighted)
     uint32_t* d_bw1w;  // entry lists of spingtp_backward_v1_weighted, nullptr if not built
     spingtp::Bw1wShape bw1w;
+    const uint32_t* d_cw;  // table of the shared-x2 block kernels (channel_blocks.hip), in d_bw1w; nullptr if none
+    spingtp::CwShape cw;
     float* d_tab_bwd;  // tables of spingtp_backward (d_tab when equal), nullptr without a backward
     bool own_tab_bwd;  // d_tab_bwd is a separate allocation
     uint32_t* d_dir;     // direct-kernel entry table of the forward (family 6), nullptr if not used
@@ -338,7 +378,7 @@ struct spingtp_plan_s {
     uint32_t* d_uvw;
     size_t uvw_off[3];
     int uvw_blocks[3], uvw_max_d3[3], uvw_paths;
-    uint32_t* d_uvwz;  // the block table of uvw_blocks.hip, nullptr where a block is too wide
+    const uint32_t* d_uvwz;  // the block table of uvw_blocks.hip, in d_uvw; nullptr where a block is too wide
     spingtp::UvwzShape uvwz;
     // mixed degrees on the large-degree kernel of the largest degree: d_aux holds the
     // degree triples of the forward, the grad_x1 and the grad_x2 launches

@@ -13,7 +13,6 @@
 #include <array>
 #include <cmath>
 #include <map>
-#include <set>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -598,9 +597,11 @@ bool build_pre_tables(int L1, int L2, int LO, const int* spins, int n_spins, uns
 }
 
 bool build_pre_tables_channel_weighted(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
-                                       int ks, std::vector<uint32_t>& out, int* n_rows) {
-    std::vector<double> T;
-    build_dense_tensor(L1, L2, LO, spins, n_spins, flags, T);
+                                       int ks, std::vector<uint32_t>& out, int* n_rows,
+                                       const std::vector<double>* dense) {
+    std::vector<double> own;
+    if (dense == nullptr) build_dense_tensor(L1, L2, LO, spins, n_spins, flags, own);
+    const std::vector<double>& T = dense != nullptr ? *dense : own;
     std::vector<std::array<int, 3>> paths;
     tensor_paths(L1, L2, LO, spins, n_spins, T, paths);
     const std::vector<int> b1 = slot_blocks(L1, spins, n_spins), b2 = slot_blocks(L2, spins, n_spins),
@@ -835,12 +836,18 @@ void tensor_paths(int L1, int L2, int LO, const int* spins, int n_spins, const s
     const std::vector<int> b1 = slot_blocks(L1, spins, n_spins), b2 = slot_blocks(L2, spins, n_spins),
                            b3 = slot_blocks(LO, spins, n_spins);
     const size_t n2 = b2.size(), n3 = b3.size();
-    std::set<std::array<int, 3>> seen;
+    const int w2 = n_spins * (L2 + 1), w3 = n_spins * (LO + 1);
+    std::vector<char> seen(static_cast<size_t>(n_spins) * (L1 + 1) * w2 * w3, 0);
     for (size_t k1 = 0; k1 < b1.size(); ++k1)
         for (size_t k2 = 0; k2 < n2; ++k2)
             for (size_t k3 = 0; k3 < n3; ++k3)
-                if (std::fabs(T[(k1 * n2 + k2) * n3 + k3]) > 1e-12) seen.insert({b1[k1], b2[k2], b3[k3]});
-    paths.assign(seen.begin(), seen.end());  // std::set orders lexicographically
+                if (std::fabs(T[(k1 * n2 + k2) * n3 + k3]) > 1e-12)
+                    seen[(static_cast<size_t>(b1[k1]) * w2 + b2[k2]) * w3 + b3[k3]] = 1;
+    paths.clear();
+    for (size_t i = 0; i < seen.size(); ++i)  // ascending, so lexicographic
+        if (seen[i])
+            paths.push_back({static_cast<int>(i / (static_cast<size_t>(w2) * w3)), static_cast<int>(i / w3 % w2),
+                             static_cast<int>(i % w3)});
 }
 
 void weight_paths(int L1, int L2, int LO, const int* spins, int n_spins, const std::vector<std::array<int, 3>>& paths,
@@ -860,6 +867,218 @@ void weight_paths(int L1, int L2, int LO, const int* spins, int n_spins, const s
                 }
                 v *= weight.at({b1[k1], b2[k2], b3[k3]});
             }
+}
+
+bool build_cw_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags, int bwd_waves,
+                    std::vector<uint32_t>& out, CwShape* shape, const std::vector<double>* dense) {
+    if (2 * std::max(L1, std::max(L2, LO)) + 1 > kCwMaxD) return false;
+    std::vector<double> own;
+    if (dense == nullptr) build_dense_tensor(L1, L2, LO, spins, n_spins, flags, own);
+    const std::vector<double>& T = dense != nullptr ? *dense : own;
+    std::vector<std::array<int, 3>> paths;
+    tensor_paths(L1, L2, LO, spins, n_spins, T, paths);
+    const int degree[3] = {L1, L2, LO};
+    int nc[3];
+    for (int ax = 0; ax < 3; ++ax) nc[ax] = n_spins * (degree[ax] + 1) * (degree[ax] + 1);
+    auto first = [&](int ax, int b) {
+        const int n = degree[ax] + 1, i = b / n, l = b - i * n;
+        return i * n * n + l * l;
+    };
+    auto width = [&](int ax, int b) { return 2 * (b % (degree[ax] + 1)) + 1; };
+    auto stride = [](int d) { return d == 1 ? 1 : (d == 3 ? 4 : 8); };
+    auto value = [&](int k1, int k2, int k3) {
+        const double v = T[(static_cast<size_t>(k1) * nc[1] + k2) * nc[2] + k3];
+        return std::fabs(v) <= 1e-12 ? 0.f : static_cast<float>(v);  // quadrature round-off of an exact zero
+    };
+    auto bits = [](float v) {
+        uint32_t w = 0;
+        std::memcpy(&w, &v, 4);
+        return w;
+    };
+    const int np = static_cast<int>(paths.size());
+    CwShape& s = *shape;
+    s = CwShape{};
+    s.np = np;
+    s.dmax = 2 * std::max(L1, LO) + 1;
+    s.bwd_waves = bwd_waves;
+    s.nc1 = nc[0];
+    s.nc2 = nc[1];
+    s.nco = nc[2];
+    out.assign(kCwHeader, 0u);
+    out[0] = static_cast<uint32_t>(np);
+    for (int ax = 0; ax < 3; ++ax) out[1 + ax] = static_cast<uint32_t>(nc[ax]);
+    auto append = [&](int at, const std::vector<uint32_t>& w) {
+        out.resize((out.size() + 3) / 4 * 4, 0u);
+        out[at] = static_cast<uint32_t>(out.size());
+        out.insert(out.end(), w.begin(), w.end());
+    };
+    std::vector<double> load(bwd_waves, 0.0);  // of the gradients' waves, continued by the tiles
+    for (int role = 0; role < 2; ++role) {
+        const int waves = role == 0 ? kCwFwdWaves : bwd_waves, ax_o = role == 0 ? 2 : 0, ax_i = role == 0 ? 0 : 2;
+        std::map<int, std::vector<int>> by;
+        for (int p = 0; p < np; ++p) by[paths[p][ax_o]].push_back(p);
+        auto cost = [&](int p) {
+            return 8.0 + width(ax_i, paths[p][ax_i]) * (3.0 + width(ax_o, paths[p][ax_o]));
+        };
+        struct Block {
+            int b, part;
+            std::vector<int> p;
+            double cost;
+        };
+        double all = 0.0;
+        for (int p = 0; p < np; ++p) all += cost(p);
+        std::vector<Block> blocks;
+        s.parts[role] = 1;
+        for (auto& kv : by) {  // paths by contracted width; more than a wave's share goes to two waves
+            std::stable_sort(kv.second.begin(), kv.second.end(),
+                             [&](int a, int b) { return width(ax_i, paths[a][ax_i]) < width(ax_i, paths[b][ax_i]); });
+            double c = 0.0;
+            for (const int p : kv.second) c += cost(p);
+            const int n = c > all / waves && kv.second.size() > 1 ? 2 : 1;
+            s.parts[role] = std::max(s.parts[role], n);
+            for (int part = 0; part < n; ++part) {
+                Block k{kv.first, part, {}, 0.0};
+                for (size_t i = part; i < kv.second.size(); i += n) {
+                    k.p.push_back(kv.second[i]);
+                    k.cost += cost(kv.second[i]);
+                }
+                if (k.p.size() > 64) return false;
+                blocks.push_back(k);
+            }
+        }
+        std::stable_sort(blocks.begin(), blocks.end(), [](const Block& a, const Block& b) { return a.cost > b.cost; });
+        std::vector<std::vector<int>> of(waves);
+        std::vector<double> l(waves, 0.0);
+        for (size_t i = 0; i < blocks.size(); ++i) {
+            const int w = static_cast<int>(std::min_element(l.begin(), l.end()) - l.begin());
+            of[w].push_back(static_cast<int>(i));
+            l[w] += blocks[i].cost;
+        }
+        if (role == 1) load = l;
+        out[4 + role] = static_cast<uint32_t>(s.parts[role]);
+        std::vector<uint32_t> sched = {0u}, bw, rw, iw;
+        int kmax = 0;
+        for (int w = 0; w < waves; ++w) {
+            for (const int bi : of[w]) {
+                const Block& blk = blocks[bi];
+                const int fo = first(ax_o, blk.b), d_o = width(ax_o, blk.b), ks = stride(d_o);
+                const uint32_t head[3] = {static_cast<uint32_t>(fo) | (static_cast<uint32_t>(d_o) << 16),
+                                          static_cast<uint32_t>(rw.size() / 4), static_cast<uint32_t>(blk.p.size())};
+                bw.insert(bw.end(), head, head + 3);
+                bw.push_back(static_cast<uint32_t>(iw.size() / 4));
+                const size_t items0 = iw.size() / 4;
+                uint32_t counts = 0;
+                int koff = 0;
+                for (const int p : blk.p) {
+                    const int fi = first(ax_i, paths[p][ax_i]), d_i = width(ax_i, paths[p][ax_i]);
+                    const int f2 = first(1, paths[p][1]), d2 = width(1, paths[p][1]);
+                    counts += 1u << (8 * (d_i / 2));
+                    koff = ks > 1 ? (koff + 3) / 4 * 4 : koff;
+                    const uint32_t r[4] = {static_cast<uint32_t>(p), static_cast<uint32_t>(fi),
+                                           static_cast<uint32_t>(koff), 0u};
+                    rw.insert(rw.end(), r, r + 4);
+                    for (int i = 0; i < d_i; ++i)
+                        for (int o = 0; o < d_o; ++o) {
+                            uint32_t slot[2] = {static_cast<uint32_t>(nc[1]), static_cast<uint32_t>(nc[1])};
+                            float v[2] = {0.f, 0.f};
+                            int n = 0;
+                            for (int k2 = f2; k2 < f2 + d2; ++k2) {
+                                const float t = role == 0 ? value(fi + i, k2, fo + o) : value(fo + o, k2, fi + i);
+                                if (t == 0.f) continue;
+                                if (n == 2) return false;  // the real bases couple at most two
+                                slot[n] = static_cast<uint32_t>(k2);
+                                v[n++] = t;
+                            }
+                            const uint32_t it[4] = {slot[0] | (slot[1] << 16), bits(v[0]), bits(v[1]),
+                                                    static_cast<uint32_t>(koff + i * ks + o)};
+                            iw.insert(iw.end(), it, it + 4);
+                        }
+                    koff += d_i * ks;
+                }
+                kmax = std::max(kmax, koff);
+                const uint32_t tail[4] = {static_cast<uint32_t>(iw.size() / 4 - items0), counts,
+                                          static_cast<uint32_t>(blk.part), 0u};
+                bw.insert(bw.end(), tail, tail + 4);
+            }
+            sched.push_back(static_cast<uint32_t>(bw.size() / 8));
+        }
+        s.kfloats[role] = (kmax + 3) / 4 * 4;
+        append(8 + 4 * role, sched);
+        append(9 + 4 * role, bw);
+        append(10 + 4 * role, rw);
+        append(11 + 4 * role, iw);
+    }
+    // grad_x2: rows (path, x1 slot) by the spin index of the path's output block, 16 per tile
+    struct Tile {
+        uint32_t col;
+        std::vector<uint32_t> rows;
+    };
+    std::vector<Tile> tiles;
+    std::vector<std::pair<int, int>> where(np);  // tile and row of a path's first x1 slot
+    for (int spin = 0; spin < n_spins; ++spin) {
+        Tile t{static_cast<uint32_t>(spin * (LO + 1) * (LO + 1)), {}};
+        for (int p = 0; p < np; ++p) {
+            if (paths[p][2] / (LO + 1) != spin) continue;
+            const int f1 = first(0, paths[p][0]), d1 = width(0, paths[p][0]);
+            for (int k = f1; k < f1 + d1; ++k) {
+                if (t.rows.size() == 16) {
+                    tiles.push_back(t);
+                    t.rows.clear();
+                }
+                if (k == f1) where[p] = {static_cast<int>(tiles.size()), static_cast<int>(t.rows.size())};
+                t.rows.push_back(static_cast<uint32_t>(p) | (static_cast<uint32_t>(k) << 16));
+            }
+        }
+        if (!t.rows.empty()) tiles.push_back(t);
+    }
+    // the tiles go to the waves with least work; `place` is a tile's position in that order
+    std::vector<std::vector<int>> of(bwd_waves);
+    for (size_t t = 0; t < tiles.size(); ++t) {
+        const int w = static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
+        of[w].push_back(static_cast<int>(t));
+        load[w] += 150.0;  // about that many of the block kernel's instructions
+    }
+    std::vector<int> place(tiles.size());
+    std::vector<uint32_t> sched = {0u}, rows, cols;
+    for (int w = 0; w < bwd_waves; ++w) {
+        for (const int t : of[w]) {
+            place[t] = static_cast<int>(cols.size());
+            std::vector<uint32_t> r = tiles[t].rows;
+            r.resize(16, static_cast<uint32_t>(np) | (static_cast<uint32_t>(nc[0]) << 16));
+            rows.insert(rows.end(), r.begin(), r.end());
+            cols.push_back(tiles[t].col);
+        }
+        sched.push_back(static_cast<uint32_t>(cols.size()));
+    }
+    s.tiles = static_cast<int>(tiles.size());
+    const size_t w2 = static_cast<size_t>(n_spins) * (L2 + 1), w3 = static_cast<size_t>(n_spins) * (LO + 1);
+    std::vector<int> index(static_cast<size_t>(n_spins) * (L1 + 1) * w2 * w3, -1);
+    for (int p = 0; p < np; ++p) index[(paths[p][0] * w2 + paths[p][1]) * w3 + paths[p][2]] = p;
+    const std::vector<int> b1 = slot_blocks(L1, spins, n_spins), b2 = slot_blocks(L2, spins, n_spins),
+                           b3 = slot_blocks(LO, spins, n_spins);
+    std::vector<uint32_t> seg = {0u}, ent;
+    for (int k2 = 0; k2 < nc[1]; ++k2) {
+        for (int k1 = 0; k1 < nc[0]; ++k1)
+            for (int k3 = 0; k3 < nc[2]; ++k3) {
+                const float v = value(k1, k2, k3);
+                if (v == 0.f) continue;
+                const int p = index[(b1[k1] * w2 + b2[k2]) * w3 + b3[k3]];
+                const int row = where[p].second + k1 - first(0, paths[p][0]), tile = where[p].first + row / 16;
+                const int col = k3 - static_cast<int>(tiles[tile].col);
+                if (col >= 16) return false;
+                ent.push_back(static_cast<uint32_t>(256 * place[tile] + 16 * (row % 16) + col));
+                ent.push_back(bits(v));
+            }
+        seg.push_back(static_cast<uint32_t>(ent.size() / 2));
+    }
+    s.nnz = static_cast<int>(ent.size() / 2);
+    append(16, rows);
+    append(17, cols);
+    append(18, seg);
+    append(19, ent);
+    out[20] = static_cast<uint32_t>(tiles.size());
+    append(21, sched);
+    return true;
 }
 
 bool unrolled_values(const UnrolledKernel& k, int role, int n1, int n2, int n3, const std::vector<double>& T,
@@ -1425,15 +1644,25 @@ struct PlanHost {
     int spin_mode = 0, dir_lds = 0;
     const spingtp::KernelEntry *k = nullptr, *kd = nullptr, *kv1 = nullptr, *kw = nullptr;
     std::vector<double> tab, tab_bwd;
-    std::vector<uint32_t> aux, pre, pre_bwd, dir, dir_b1, dir_b2, pre_w, bw1w, uvw, uvwz;
+    std::vector<uint32_t> aux, pre, pre_bwd, dir, dir_b1, dir_b2, pre_w, bw1w, uvw;
+    size_t cw_off = 0, uvwz_off = 0;  // first word of the block kernels' tables in bw1w and uvw (0: none)
     size_t uvw_off[3] = {0, 0, 0};  // first word of each role's table in uvw
     bool padded = false;            // mixed degrees on the large-degree kernel (aux: 3 degree triples)
     spingtp::Bw1wShape bw1w_shape{};
     spingtp::UvwzShape uvwz_shape{};
+    spingtp::CwShape cw_shape{};
     const spingtp::UnrolledKernel* unrolled = nullptr;
     size_t unrolled_off[3] = {0, 0, 0};
     bool has_backward = false, same_bwd = false;
 };
+
+// Appends a table to one that is uploaded with it, on a 64-byte boundary; its first word.
+size_t append_table(std::vector<uint32_t>& to, const std::vector<uint32_t>& table) {
+    const size_t at = (to.size() + 15) / 16 * 16;
+    to.resize(at, 0u);
+    to.insert(to.end(), table.begin(), table.end());
+    return at;
+}
 
 // weights: one per path of spingtp_paths_host (n_weights of them), or nullptr for the
 // unweighted product.
@@ -1542,26 +1771,38 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
         if (k != nullptr && k->family == 6)
             spingtp::build_direct_table(L1, L2, Lout, spins, n_spins, basis, 0, dir, &lds_floats, &dense);
         if (channel_weights) {  // path slots first, then the instantiation that holds them
+            if (dense.empty()) spingtp::build_dense_tensor(L1, L2, Lout, spins, n_spins, basis, dense);
             const int nc2 = n_spins * (L2 + 1) * (L2 + 1), nco = n_spins * (Lout + 1) * (Lout + 1);
             const int nc1 = n_spins * (L1 + 1) * (L1 + 1);
             int rows = 0, ks = 0, nt = 0;
             if (nc2 <= spingtp::kPreMaxNC) {
                 // with ks = 0 the builder only counts the path slots
                 (void)spingtp::build_pre_tables_channel_weighted(L1, L2, Lout, spins, n_spins, basis, 0, pre_w,
-                                                                 &rows);
+                                                                 &rows, &dense);
                 kw = spingtp::find_pre_weighted_kernel((std::max(rows, nc1) + 15) / 16, (nco + 15) / 16,
                                                        static_cast<int>(dtype), &ks, &nt);
             }
             if (kw == nullptr ||
-                !spingtp::build_pre_tables_channel_weighted(L1, L2, Lout, spins, n_spins, basis, ks, pre_w, &rows)) {
+                !spingtp::build_pre_tables_channel_weighted(L1, L2, Lout, spins, n_spins, basis, ks, pre_w, &rows,
+                                                            &dense)) {
                 kw = nullptr;
                 pre_w.clear();
             }
             // the gradients (spingtp_backward_v1_weighted) where their tiles fit; a plan
             // needs the forward or the gradients
-            if (!spingtp::build_bwd_v1w_table(L1, L2, Lout, spins, n_spins, basis, bw1w, &bw1w_shape))
+            if (!spingtp::build_bwd_v1w_table(L1, L2, Lout, spins, n_spins, basis, bw1w, &bw1w_shape, &dense))
                 bw1w.clear();
             if (pre_w.empty() && bw1w.empty()) return SPINGTP_ERR_UNSUPPORTED;
+            // the block kernels; their gradients with 8 waves where two workgroups then fit a CU
+            std::vector<uint32_t> cw;
+            for (int waves = 8; !bw1w.empty() && waves <= 16; waves *= 2) {
+                if (!spingtp::build_cw_table(L1, L2, Lout, spins, n_spins, basis, waves, cw, &h.cw_shape, &dense)) {
+                    cw.clear();
+                    break;
+                }
+                if (2 * spingtp::cw_bwd_lds_floats(h.cw_shape) <= spingtp::kBw1wMaxLdsFloats) break;
+            }
+            if (!cw.empty()) h.cw_off = append_table(bw1w, cw);
         }
         if (kd != nullptr && !fourier_bwd) {
             spingtp::build_direct_table(L1, L2, Lout, spins, n_spins, basis, 1, dir_b1, &lds_floats, &dense);
@@ -1578,15 +1819,12 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
             std::vector<uint32_t>* const tables[3] = {&dir, &dir_b1, &dir_b2};
             for (int role = 0; un != nullptr && role < 3; ++role) {
                 if (tables[role]->empty()) continue;
-                const size_t at = (tables[role]->size() + 15) / 16 * 16;  // a cache line of values starts each list
                 std::vector<uint32_t> words;
                 const int n = n_spins * (L1 + 1) * (L1 + 1);
                 if (!spingtp::unrolled_values(*un, role, n, n, n, dense, words)) continue;
-                tables[role]->resize(at, 0u);
-                tables[role]->insert(tables[role]->end(), words.begin(), words.end());
-                tables[role]->resize(tables[role]->size() + 32, 0u);
+                words.resize(words.size() + 32, 0u);
                 h.unrolled = un;
-                h.unrolled_off[role] = at;
+                h.unrolled_off[role] = append_table(*tables[role], words);
             }
         }
         if (k != nullptr && k->family == 4) spingtp::build_mfma_operands(L1, aux);
@@ -1600,9 +1838,10 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
                 h.uvw_off[role] = h.uvw.size();
                 h.uvw.insert(h.uvw.end(), t.begin(), t.end());
             }
-            if (!spingtp::build_uvw_blocks_table(L1, L2, Lout, spins, n_spins, basis, h.uvwz, &h.uvwz_shape, &dense) ||
-                !spingtp::uvwz_fits(h.uvwz_shape))
-                h.uvwz.clear();
+            std::vector<uint32_t> uvwz;
+            if (spingtp::build_uvw_blocks_table(L1, L2, Lout, spins, n_spins, basis, uvwz, &h.uvwz_shape, &dense) &&
+                spingtp::uvwz_fits(h.uvwz_shape))
+                h.uvwz_off = append_table(h.uvw, uvwz);
         }
         if (kv1->family == 5 &&
             !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre, false, weighted ? &dense : nullptr))
@@ -1635,7 +1874,7 @@ struct DeviceApi {
 struct PlanDevice {
     float *tab = nullptr, *tab_bwd = nullptr;
     uint32_t *aux = nullptr, *pre = nullptr, *pre_bwd = nullptr, *dir = nullptr, *dir_b1 = nullptr,
-             *dir_b2 = nullptr, *pre_w = nullptr, *bw1w = nullptr, *uvw = nullptr, *uvwz = nullptr;
+             *dir_b2 = nullptr, *pre_w = nullptr, *bw1w = nullptr, *uvw = nullptr;
 };
 
 // Uploads every non-empty table (fp32 tables rounded to nearest).  On any failure every
@@ -1667,8 +1906,7 @@ spingtp_status upload_plan(const PlanHost& h, const DeviceApi& api, PlanDevice& 
     }
     const std::pair<const std::vector<uint32_t>*, uint32_t**> words[] = {
         {&h.aux, &d.aux}, {&h.pre, &d.pre}, {&h.pre_bwd, &d.pre_bwd}, {&h.dir, &d.dir}, {&h.dir_b1, &d.dir_b1},
-        {&h.dir_b2, &d.dir_b2}, {&h.pre_w, &d.pre_w}, {&h.bw1w, &d.bw1w}, {&h.uvw, &d.uvw},
-        {&h.uvwz, &d.uvwz}};
+        {&h.dir_b2, &d.dir_b2}, {&h.pre_w, &d.pre_w}, {&h.bw1w, &d.bw1w}, {&h.uvw, &d.uvw}};
     for (const auto& w : words)
         put(w.first->data(), w.first->size() * sizeof(uint32_t), reinterpret_cast<void**>(w.second));
     if (fail == 0) return SPINGTP_OK;
@@ -1708,7 +1946,7 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
         for (void* q : {static_cast<void*>(d.tab), static_cast<void*>(d.tab_bwd), static_cast<void*>(d.aux),
                         static_cast<void*>(d.pre), static_cast<void*>(d.pre_bwd), static_cast<void*>(d.dir),
                         static_cast<void*>(d.dir_b1), static_cast<void*>(d.dir_b2), static_cast<void*>(d.pre_w),
-                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw), static_cast<void*>(d.uvwz)})
+                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw)})
             if (q != nullptr) (void)hipFree(q);
         return SPINGTP_ERR_OUT_OF_MEMORY;
     }
@@ -1738,8 +1976,10 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
     p->kernel_v1w = d.pre_w != nullptr ? h.kw : nullptr;
     p->d_bw1w = d.bw1w;
     p->bw1w = h.bw1w_shape;
+    p->d_cw = h.cw_off != 0 ? d.bw1w + h.cw_off : nullptr;
+    p->cw = h.cw_shape;
     p->d_uvw = d.uvw;
-    p->d_uvwz = d.uvwz;
+    p->d_uvwz = h.uvwz_off != 0 ? d.uvw + h.uvwz_off : nullptr;
     p->uvwz = h.uvwz_shape;
     for (int role = 0; role < 3; ++role) {
         const size_t o = h.uvw_off[role];
@@ -1791,7 +2031,7 @@ extern "C" spingtp_status spingtp_plan_upload_selftest_host(int L1, int L2, int 
         for (void* q : {static_cast<void*>(d.tab), static_cast<void*>(d.tab_bwd), static_cast<void*>(d.aux),
                         static_cast<void*>(d.pre), static_cast<void*>(d.pre_bwd), static_cast<void*>(d.dir),
                         static_cast<void*>(d.dir_b1), static_cast<void*>(d.dir_b2), static_cast<void*>(d.pre_w),
-                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw), static_cast<void*>(d.uvwz)})
+                        static_cast<void*>(d.bw1w), static_cast<void*>(d.uvw)})
             if (q != nullptr) api.release(api.ctx, q);
     return su;
 }
@@ -1854,7 +2094,6 @@ spingtp_status spingtp_plan_destroy(spingtp_plan plan) {
     release(plan->d_pre);
     release(plan->d_pre_bwd);
     release(plan->d_uvw);
-    release(plan->d_uvwz);
     if (plan->own_tab_bwd) release(plan->d_tab_bwd);
     if (switched) (void)hipSetDevice(cur);
     delete plan;

@@ -479,3 +479,23 @@ def test_depthwise_rules():
         plan.forward_depthwise(x1, torch.zeros((2, 0, 3, 9), device="cuda"), torch.zeros((0, 3, n), device="cuda"))
     with pytest.raises(ValueError):  # one weight slice per second-input channel
         plan.forward_depthwise(x1, torch.zeros((2, 2, 3, 9), device="cuda"), torch.zeros((1, 3, n), device="cuda"))
+
+
+@pytest.mark.parametrize("L1,L2,LO,spins,N,C,V,basis,dtype", [
+    (2, 2, 2, S3, 3, 1, 1, 0, "fp32"),       # one channel; blocks split over two waves
+    (2, 2, 2, S3, 5, 64, 2, 1, "fp32"),      # one whole 64-channel tile: grad_x2 without partial sums
+    (2, 2, 2, S3, 5, 65, 1, 2, "fp32"),      # two tiles, the second with one channel
+    (1, 3, 3, S3, 7, 63, 5, 2, "bf16"),      # more second-input channels than a launch takes
+    (3, 3, 3, S3, 4, 20, 1, 2, "fp32"),      # blocks of 7 slots; gradients on the entry lists (LDS)
+    (3, 3, 3, (0,), 530, 3, 1, 0, "fp32"),   # more edges than workgroups: several edges per range
+    (2, 2, 2, S5, 3, 5, 1, 0, "fp32"),       # invalid blocks of three slots
+    (1, 1, 1, S3, 9, 70, 1, 0, "fp32"),      # forward on the entry lists (few entries), gradients on blocks
+    (0, 2, 2, S3, 2, 4, 1, 0, "fp32"),       # blocks of one slot
+])
+def test_channel_block_kernel_edges(L1, L2, LO, spins, N, C, V, basis, dtype):
+    """Edges of the block kernels' tiles (64 channels, split blocks, edge ranges) and both sides
+    of their dispatch, forward and gradients against the oracle."""
+    run_depthwise(L1, L2, LO, spins, N, C, V, basis, dtype, seed=N + C)
+    if V == 1:
+        run_channel_weighted(L1, L2, LO, spins, N, C, basis, dtype, seed=C)
+        run_channel_weighted_backward(L1, L2, LO, spins, N, C, basis, dtype, seed=C)
