@@ -13,13 +13,10 @@ SOURCES = ["plan.cpp", "api.cpp", "forward.hip", "forward_big_parity.hip", "forw
            "forward_big_parity_padded.hip", "forward_mfma.hip", "forward_pre.hip",
            "forward_pre_large.hip", "forward_pre_weighted.hip", "forward_direct.hip", "backward.hip", "backward_v1w.hip", "forward_uvw.hip",
            "uvw_blocks.hip", "channel_blocks.hip", "direct_unrolled_paper.hip", "direct_unrolled_paired.hip", "direct_unrolled_parity.hip"]
-# per-source additions: the parity-basis large-degree kernels schedule for fewer registers
-# (they spill less and run 22-35 % faster that way; the other kernels run slower with it)
-_MINREG = ["-mllvm", "-amdgpu-sched-strategy=iterative-minreg"]
+# per-source additions
 # the compile-time tensor patterns take more constant-evaluation steps than the default limit
 _CONSTEXPR = ["-fconstexpr-steps=200000000"]
-EXTRA_FLAGS = {"forward_big_parity.hip": _MINREG, "forward_big_parity_padded.hip": _MINREG,
-               "direct_unrolled_paper.hip": _CONSTEXPR, "direct_unrolled_paired.hip": _CONSTEXPR,
+EXTRA_FLAGS = {"direct_unrolled_paper.hip": _CONSTEXPR, "direct_unrolled_paired.hip": _CONSTEXPR,
                "direct_unrolled_parity.hip": _CONSTEXPR}
 
 # -packed-fp32-ops: no v_pk_{add,mul,fma}_f32 in generated code.

@@ -2,8 +2,7 @@
 // a plan with degrees (L1, L2, Lout) whose rows exceed the direct kernel's runs on the
 // kernel of L = max(L1, L2, Lout), 9..16, with x1 and x2 zero-padded as they are staged
 // and the product truncated to Lout as it is stored.  Paper basis with spins
-// {-1, 0, +1} and spin {0} here; the parity-basis ones, built with the
-// register-minimising scheduler like their equal-degree counterparts, are in
+// {-1, 0, +1} and spin {0} here; the parity-basis ones are in
 // forward_big_parity_padded.hip.  A translation unit of its own so that it compiles
 // beside forward.hip.
 #include <hip/hip_runtime.h>

@@ -1,7 +1,5 @@
 // The mixed-degree instantiations of the parity-basis large-degree kernel (spins
-// {-1, 0, +1}, L = 9..16, fp32 and bf16 I/O; PAD in forward_pair.h), built with the
-// register-minimising scheduling strategy like the equal-degree ones in
-// forward_big_parity.hip.
+// {-1, 0, +1}, L = 9..16, fp32 and bf16 I/O; PAD in forward_pair.h).
 #include <hip/hip_runtime.h>
 
 #include "forward_pair.h"

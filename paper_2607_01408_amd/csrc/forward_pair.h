@@ -268,10 +268,27 @@ __device__ __forceinline__ void theta_sums_zero(ThetaSums<L, SPIN>& a) {
     a.wpl = a.wmi = 0.f;
 }
 
+// The node's table values sit in registers, word w in lane w % 64 of tv[w / 64], and reach the
+// FMAs as scalars by readlane.  Scalar loads would share their wait counter with the LDS reads
+// of the rows and complete out of order, so every row read would also wait for the tables.
+template <int L>
+struct ThetaTable {
+    static constexpr int WORDS = make_layout(L, 0, 0).aw + L + 1;
+    static constexpr int N = (WORDS + 63) / 64;
+    float tv[N];
+    __device__ __forceinline__ void load(const float* __restrict__ tb, int lane) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) tv[i] = 64 * i + lane < WORDS ? tb[64 * i + lane] : 0.f;
+    }
+    __device__ __forceinline__ float operator[](int w) const {
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tv[w / 64]), w % 64));
+    }
+};
+
 // s: the lane's staged row, block b (spins -1, 0, +1, or 0 alone) at s + b CW with
 // CW = LB^2 - LA^2 slots, slot q of a block at offset q - LA^2.
-template <int L, bool SPIN, bool PAR, int LA, int LB>
-__device__ __forceinline__ void theta_sums_add(const float* s, const float* __restrict__ tb, ThetaSums<L, SPIN>& a) {
+template <int L, bool SPIN, bool PAR, int LA, int LB, typename Table>
+__device__ __forceinline__ void theta_sums_add(const float* s, Table tb, ThetaSums<L, SPIN>& a) {
     constexpr Layout Y = make_layout(L, 0, 0);
     constexpr int CW = LB * LB - LA * LA, O = LA * LA;
     const float* x0 = s + (SPIN ? CW : 0);
@@ -314,6 +331,13 @@ __device__ __forceinline__ void theta_sums_add(const float* s, const float* __re
             a.wmi = fmaf(vm_of(l * l + l), w, a.wmi);
         }
     }
+}
+
+// The same with the tables by scalar loads (restrict: they may move over the LDS traffic).
+template <int L, bool SPIN, bool PAR, int LA, int LB>
+__device__ __forceinline__ void theta_sums_add_scalar(const float* s, const float* __restrict__ tb,
+                                                      ThetaSums<L, SPIN>& a) {
+    theta_sums_add<L, SPIN, PAR, LA, LB>(s, tb, a);
 }
 
 // The step-(A) outputs from the finished sums (the closing steps of coef_to_theta_fourier).
@@ -379,12 +403,29 @@ __device__ __forceinline__ void pair_publish(float* D, int sub, const float (&Q0
 // input rows in LDS a chunk of degrees at a time (coalesced loads, the next
 // chunk's loads in flight while the waves work on the current one) and every
 // lane pair runs step (A) for its wave's node from there; the spectra of the
-// round are then exchanged in LDS (the same region), and every output group's
-// owner lane accumulates the round's contribution into the output row (written
-// in round 0, then read, added and written by the same lane in later rounds:
-// ordered, deterministic).  The output rows of the tile live in LDS across the
-// rounds and leave in one coalesced store.
+// round are then exchanged in LDS (the same region), and step (E) adds the round's
+// contribution to the output rows of the tile, which live in LDS across the rounds
+// (written in round 0, then read, added and written by the same lane in the same
+// order: deterministic) and leave in one coalesced store.
+//
+// Step (E) from L = 11 on (big_matrix_projection) contracts the round's nodes of each output group (t, kind): a matrix
+// product with the orders l of the group as rows, the records of the round as the
+// contraction and the units as columns, on v_mfma_f32_16x16x4f32 (two of them cover
+// 8 records; the result is bit for bit that of the chain of FMAs over the records).
+// A group's cost is then the same whatever its number of orders, so the groups go
+// round the waves by index.  With one lane per output order of a unit and the
+// groups unrolled under a branch per wave, it took 27% of the kernel at L = 12: the
+// code of all groups passed through the instruction cache in every round, and each
+// spectrum value was read by every order's lane.
+//
+// Bound by the vector units (steps A, C, D) with one workgroup of W waves per CU (the
+// LDS tile allows no second one).  262,144 units, fp32, paper basis, before -> with
+// step (E) on the matrix units and the tables of step (A) in registers:
+// L = 11 1.89 -> 1.66 ms, 12 2.59 -> 2.06, 14 4.07 -> 2.84, 16 6.93 -> 4.51; parity basis 12
+// 2.56 -> 2.13, 16 7.27 -> 4.79 (with the default scheduling strategy).
 // ---------------------------------------------------------------------------
+typedef float v4fe __attribute__((ext_vector_type(4)));
+
 template <int L, bool SPIN, int W>
 struct BigShape {
     using PS = PairShape<L, SPIN>;
@@ -415,10 +456,11 @@ struct BigShape {
         return (W * UNITS * pwidth(K) + TRIG + UNITS * STO) * 4 <= 160 * 1024;
     }
     static constexpr int K = fits(1) ? 1 : fits(2) ? 2 : fits(3) ? 3 : fits(4) ? 4 : 1;
-    static constexpr bool OUT_LDS = fits(K);
+    static_assert(fits(K), "the output tile stays in LDS");
+    static_assert(W <= 8, "step (E) contracts up to 8 records a round");
     static constexpr int DSP = pwidth(K);  // record stride of one part
     static constexpr int DF = W * UNITS * DSP;
-    static constexpr int LDS_FLOATS = DF + TRIG + (OUT_LDS ? UNITS * STO : 0);
+    static constexpr int LDS_FLOATS = DF + TRIG + UNITS * STO;
     __host__ __device__ static constexpr int part_of_t(int t) {
         int k = 0;
         while (k + 1 < K && t >= tlo(k + 1, K)) ++k;
@@ -457,32 +499,6 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-// Owners of the output groups with several spectrum parts: each part's groups are
-// spread over the waves by size (largest first, least-loaded wave).
-template <int L, bool SPIN, int NW, int K>
-constexpr Owners<PairShape<L, SPIN>::NG> assign_part_owners() {
-    using P = PairShape<L, SPIN>;
-    using B = BigShape<L, SPIN, NW>;
-    Owners<P::NG> o{};
-    for (int k = 0; k < K; ++k) {
-        int load[NW] = {};
-        bool done[P::NG] = {};
-        for (;;) {
-            int best = -1;
-            for (int g = 0; g < P::NG; ++g)
-                if (!done[g] && B::part_of_t(P::t_of(g)) == k && (best < 0 || P::size(g) > P::size(best))) best = g;
-            if (best < 0) break;
-            int w = 0;
-            for (int q = 1; q < NW; ++q)
-                if (load[q] < load[w]) w = q;
-            o.owner[best] = w;
-            load[w] += P::size(best);
-            done[best] = true;
-        }
-    }
-    return o;
-}
-
 // pair_publish restricted to the orders t in [T_LO, T_HI), slot s stored at s - sbase(T_LO).
 template <int L, bool SPIN, int T_LO, int T_HI>
 __device__ __forceinline__ void pair_publish_part(float* D, int sub, const float (&Q0)[L + 1],
@@ -504,25 +520,39 @@ __device__ __forceinline__ void pair_publish_part(float* D, int sub, const float
     }
 }
 
-// Whether the last round splits its nodes' phi points over the idle waves.  Measured
-// on 262,144 units: it pays wherever the last round leaves waves idle, except where
-// the extra per-round state costs spills (paper basis L = 9: 0.89 -> 0.96 ms;
-// parity basis L = 12: 2.67 -> 2.93 ms; the scalar-spin kernels up to L = 13).
-template <int L, bool SPIN, bool PAR>
+// Whether the last round splits its nodes' phi points over the idle waves, for the
+// degrees whose last round leaves half of them or more idle (11, 12, 13 and 16).
+// Measured on 131,072 units, fp32, without -> with: paper basis 0.904 -> 0.834 ms at
+// L = 11, 1.026 -> 1.037 at 12, 1.233 -> 1.223 at 13, 2.346 -> 2.272 at 16; parity basis
+// 0.928 -> 0.882, 1.079 -> 1.069, 1.286 -> 1.275, 2.477 -> 2.406.  Spin {0} has little
+// work per point: 0.226 -> 0.233, 0.256 -> 0.278, 0.292 -> 0.307, 0.559 -> 0.543.
+template <int L, bool SPIN>
 constexpr bool big_split_last() {
-    if (!SPIN) return L == 16;
-    if (PAR) return L == 11 || L == 13 || L == 14 || L == 16;
-    return L >= 11;
+    return L >= (SPIN ? 11 : 16);
 }
 
 // Whether the staging loads may stay hoisted out of the round loop: the compiler then
-// loads every chunk's rows once per tile and keeps them in registers, which pays
-// where they fit without spilling (L = 9 0.88 against 1.01 ms, L = 12 2.61 against
-// 2.80 on 262,144 units; from L = 13 on they spill 22-61 VGPRs, and the scalar-spin
-// kernels gain nothing).
-template <int L, bool SPIN, bool PAR>
+// loads every chunk's rows once per tile and keeps them in registers.  131,072 units,
+// fp32, paper basis, in the loop -> hoisted: 0.503 -> 0.488 ms at L = 9, 0.562 -> 0.571 at
+// 10, 0.876 -> 0.834 at 11, 1.080 -> 1.037 at 12, 1.223 -> 1.211 at 13 (parity basis
+// 1.275 -> 1.308); from there on they spill (1.425 -> 1.480 at 14, 2.272 -> 3.406 at 16),
+// and the scalar-spin kernels gain nothing.
+template <int L, bool SPIN>
 constexpr bool big_hoist_rows() {
     return SPIN && L <= 12;
+}
+
+// Whether step (E) runs on the matrix units and step (A) reads its tables from registers
+// (ThetaTable), or each output group's owner lanes add its records and the tables come by
+// scalar loads.  With few orders per group the 16-row tiles are mostly padding and the
+// unrolled groups fit the instruction cache.  131,072 units, fp32, owners and scalar loads ->
+// matrix units and registers: paper basis 0.438 -> 0.488 ms at L = 9, 0.533 -> 0.560 at 10,
+// 0.943 -> 0.834 at 11, 1.295 -> 1.037 at 12; parity basis 0.507 -> 0.514, 0.623 -> 0.591,
+// 1.083 -> 0.932, 1.285 -> 1.070; spin {0} 0.174 -> 0.226 at L = 11, 0.256 -> 0.255 at 12,
+// 0.307 -> 0.290 at 13.
+template <int L, bool SPIN>
+constexpr bool big_matrix_projection() {
+    return L >= (SPIN ? 11 : 12);
 }
 
 // PAR (spins only): the plan's basis is the parity-labelled one; a separate
@@ -530,7 +560,7 @@ constexpr bool big_hoist_rows() {
 // paper-basis kernels registers.
 // zero: 0 from the launcher.  The input rows are the same in every round, so the
 // compiler hoists the staging loads of all chunks out of the round loop; where they
-// do not fit in registers it holds them in scratch (106 spilled VGPRs at L = 16).
+// do not fit in registers it holds them in scratch (60 spilled VGPRs at L = 16).
 // Offsetting them by round * zero keeps them in the loop, in flight one chunk ahead
 // (big_hoist_rows picks the degrees where the hoisted form fits).
 // TIO: float (fp32 I/O) or uint16_t (bf16 I/O: rows widened to fp32 as they are staged,
@@ -541,24 +571,24 @@ constexpr bool big_hoist_rows() {
 // exact for the products of degree <= 3 L >= L1 + L2 + Lout: the rows are staged with
 // zeros above L1 and L2 and the output tile is stored up to Lout.  A separate
 // instantiation: the run-time row strides and bounds cost the equal-degree kernels
-// registers (L = 16: 2 -> 147 spilled VGPRs).
+// registers.
 template <int L, bool SPIN, int W, bool BWD, bool PAR, typename TIO, bool PAD>
 __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_big_kernel(
     const TIO* __restrict__ x1, const TIO* __restrict__ x2, TIO* __restrict__ out, int64_t units, int64_t cpx2,
     const float* __restrict__ tab, const uint32_t* __restrict__ deg, int zero) {
     using B = BigShape<L, SPIN, W>;
     constexpr bool F32 = std::is_same<TIO, float>::value;
-    static_assert(F32 || B::OUT_LDS, "bf16 I/O needs the output tile in LDS");
-    static_assert(!PAD || B::OUT_LDS, "mixed degrees need the output tile in LDS");
     using P = typename B::PS;
     constexpr Layout Y = B::Y;
-    constexpr bool SPLIT = big_split_last<L, SPIN, PAR>();
+    constexpr bool SPLIT = big_split_last<L, SPIN>();
+    constexpr bool MATRIX = big_matrix_projection<L, SPIN>();
+    static_assert(MATRIX || (B::K == 1 && !SPLIT), "the owners' form takes whole records of whole nodes");
     constexpr int TM1 = Y.TM + 1;
     constexpr int BO = (L + 1) * (L + 1);
     __shared__ float lds[B::LDS_FLOATS];
     float* D = lds;
     float* TR = lds + B::DF;
-    float* YT = TR + B::TRIG;  // output tile (OUT_LDS only)
+    float* YT = TR + B::TRIG;  // output tile
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -567,20 +597,17 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t u0 = static_cast<int64_t>(blockIdx.x) * B::UNITS;
     const int nvalid = static_cast<int>(units - u0 < B::UNITS ? units - u0 : B::UNITS);
-    const bool valid = u < nvalid;
-    const int64_t row = u0 + (valid ? u : 0);  // invalid lanes compute on a valid row, store nothing
     const float* g = tab;
+    constexpr Owners<P::NG> own = assign_pair_owners<L, SPIN, W>();
     // slots per spin block of the x1, x2 and output rows (their degrees' (l + 1)^2)
     const int bb1 = PAD ? static_cast<int>((deg[0] + 1) * (deg[0] + 1)) : B::BB;
     const int bb2 = PAD ? static_cast<int>((deg[1] + 1) * (deg[1] + 1)) : B::BB;
     const int bbo = PAD ? static_cast<int>((deg[2] + 1) * (deg[2] + 1)) : B::BB;
-    float* orow = nullptr;  // the output row in global memory (fp32 without the LDS tile)
-    if constexpr (F32) orow = out + row * B::NC;
     // staging: TPR threads per input row (row r = lane r of every wave)
     constexpr int TPR = B::THREADS / 64;
     static_assert(B::THREADS % 64 == 0, "whole waves");
     const int sr = tid / TPR, sk = tid % TPR;
-    const int64_t srow = u0 + ((sr >> 1) < nvalid ? (sr >> 1) : 0);
+    const int64_t srow = u0 + ((sr >> 1) < nvalid ? (sr >> 1) : 0);  // past the end: a valid row, not stored
     const int sbb = (sr & 1) ? bb2 : bb1;  // this thread's row: slots per spin block
     const TIO* ssrc;
     if constexpr (PAD) ssrc = (sr & 1) ? x2 + (srow / cpx2) * (B::NS * bb2) : x1 + srow * (B::NS * bb1);
@@ -596,22 +623,17 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
     // reads them, and the finished output rows by P^T before they are final
     static_assert(SPIN || !PAR, "the parity basis only mixes |s| = 1 blocks");
     if constexpr (SPIN) {  // l = 0 slots of the |s| = 1 blocks
-        if constexpr (B::OUT_LDS) {
-            if (wave == 0) YT[u * B::STO + (sub ? 2 * BO : 0)] = 0.f;
-        } else {
-            if (wave == 0 && valid) orow[sub ? 2 * BO : 0] = 0.f;
-        }
+        if (wave == 0) YT[u * B::STO + (sub ? 2 * BO : 0)] = 0.f;
     }
     __syncthreads();
 
     constexpr int K = B::K;
-    constexpr Owners<P::NG> own = K == 1 ? assign_pair_owners<L, SPIN, W>() : assign_part_owners<L, SPIN, W, K>();
 #pragma unroll 1
     for (int r = 0; r < B::ROUNDS; ++r) {
         // A round takes nr nodes.  With SPLIT, a round with fewer nodes than waves (the
         // last one) splits each node's phi points over nsplit = W / nr waves: wave w
         // takes node r W + w % nr, part w / nr, and publishes a partial record; the
-        // owners' sum over the nw = nr nsplit records below adds the parts up.
+        // contraction over the nw = nr nsplit records below adds the parts up.
         const int nr = (B::NT - r * W) < W ? (B::NT - r * W) : W;
         const int nsplit = SPLIT ? W / nr : 1, nw = SPLIT ? nr * nsplit : nr;
         const int node = SPLIT ? r * W + wave % nr : r * W + wave;
@@ -621,13 +643,15 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
         // (A) chunk by chunk: stage the 64 rows' slots of the chunk's degrees, then
         // every wave adds them to its node's sums
         const float* tb = tab + Y.glob + (active ? node : 0) * Y.pb;
+        ThetaTable<L> table;
+        if constexpr (MATRIX) table.load(tb, lane);
         ThetaSums<L, SPIN> acc;
         theta_sums_zero(acc);
         // software pipeline: chunk c + 1's global loads are in flight while the
         // waves work on chunk c
         constexpr int IT = (B::SCAP + TPR - 1) / TPR;  // staged values per block and thread
         float pre[B::NS][IT];
-        const TIO* rsrc = big_hoist_rows<L, SPIN, PAR>() ? ssrc : ssrc + r * zero;
+        const TIO* rsrc = big_hoist_rows<L, SPIN>() ? ssrc : ssrc + r * zero;
         auto widen = [](TIO v) {
             if constexpr (F32) return v;
             else return __uint_as_float(static_cast<uint32_t>(v) << 16);
@@ -662,7 +686,10 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
                 }
             __syncthreads();
             if constexpr (c + 1 < B::NCH) fetch(std::integral_constant<int, c + 1>{});
-            if (active) theta_sums_add<L, SPIN, PAR, LA, LB>(D + lane * STR, tb, acc);
+            if (active) {
+                if constexpr (MATRIX) theta_sums_add<L, SPIN, PAR, LA, LB>(D + lane * STR, table, acc);
+                else theta_sums_add_scalar<L, SPIN, PAR, LA, LB>(D + lane * STR, tb, acc);
+            }
         };
         fetch(std::integral_constant<int, 0>{});
         for_each_index(chunk, std::make_integer_sequence<int, B::NCH>{});
@@ -682,40 +709,135 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
             }
         }
         // the round's spectra in K parts (orders t in [tlo(k), tlo(k + 1))): publish
-        // part k, then every owner of a group of part k adds the round's nodes
+        // part k, then (E) for its groups: group i by wave i % W on the matrix units, or (without
+        // them, K = 1) each group by its owner wave, which adds the round's nodes
         auto part = [&](auto kc) {
             constexpr int k = decltype(kc)::value;
             constexpr int T_LO = B::tlo(k, K), T_HI = B::tlo(k + 1, K);
+            if constexpr (!MATRIX) {
+                if (active)
+                    pair_publish_part<L, SPIN, T_LO, T_HI>(D + (wave * B::UNITS + u) * B::DSP, sub, Q0, Q1, Q2, zslot);
+                __syncthreads();
+#pragma unroll
+                for (int gi = 0; gi < P::NG; ++gi) {
+                    if (own.owner[gi] != wave) continue;
+                    const int t = P::t_of(gi), kind = P::kind_of(gi);
+                    int tab_base = Y.e0c, blk = SPIN ? BO : 0;
+                    if (kind == 1) tab_base = Y.e1p, blk = 2 * BO;
+                    if (kind == 2) tab_base = Y.e1m, blk = 0;
+                    if (kind == 3) tab_base = Y.e1z, blk = sub ? 0 : 2 * BO;
+                    float acc[L + 1];
+#pragma unroll
+                    for (int l = 0; l <= L; ++l) acc[l] = 0.f;
+#pragma unroll 1
+                    for (int jj = 0; jj < nw; ++jj) {
+                        const float d = D[(jj * B::UNITS + u) * B::DSP + P::slot(gi) + sub];
+                        const float* te = tab + Y.glob + (r * W + jj) * Y.pb;
+#pragma unroll
+                        for (int l = P::lmin(gi); l <= L; ++l)
+                            acc[l] = fmaf(te[kind == 3 ? tab_base + l : tab_base + tri(L, t, l)], d, acc[l]);
+                    }
+                    if (!(t == 0 && kind == 0 && sub)) {
+                        float* yrow = YT + u * B::STO;
+#pragma unroll
+                        for (int l = P::lmin(gi); l <= L; ++l) {
+                            float* o = yrow + blk + l * l + l + (sub ? -t : t);
+                            *o = (r == 0) ? acc[l] : *o + acc[l];
+                        }
+                    }
+                }
+                __syncthreads();
+                return;
+            }
+            // t = 0: R0, then Z (spins); every t >= 1: R0, P, M (spins) or R0.  The 17 rows of R0
+            // at t = 0 of degree 16 take a second group (l = 16 alone).
+            constexpr int G0 = T_LO == 0 ? P::G0 : 0, EXTRA = T_LO == 0 && L == 16 ? 1 : 0;
+            constexpr int NGP = G0 + P::GT * (T_HI - (T_LO > 1 ? T_LO : 1)) + EXTRA;
+            struct Group {
+                int t, kind, lmin;
+            };
+            auto group = [&](int i) {
+                if (EXTRA && i == NGP - 1) return Group{0, 0, 16};
+                if (i < G0) return Group{0, i == 0 ? 0 : 3, i == 0 ? 0 : 1};
+                const int t = (T_LO > 1 ? T_LO : 1) + (i - G0) / P::GT;
+                return Group{t, (i - G0) % P::GT, t};
+            };
+            // the group's table values: row l = lmin + lane % 16 of the nodes of records
+            // 4 s + lane / 16 (0 past the degree and the round's records)
+            const int lr = lane & 15, lq = lane >> 4;
+            auto values = [&](int i, float (&a)[2]) {
+                const Group G = group(i);
+                const int at = G.kind == 3 ? Y.e1z + G.lmin
+                                           : (G.kind == 0 ? Y.e0c : (G.kind == 1 ? Y.e1p : Y.e1m)) + tri(L, G.t, G.lmin);
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int rec = 4 * s + lq;
+                    const int nd = r * W + (SPLIT ? rec % nr : rec);
+                    a[s] = rec < nw && G.lmin + lr <= L ? tab[Y.glob + nd * Y.pb + at + lr] : 0.f;
+                }
+            };
+            float a[2], an[2];
+            int i = wave;
+            if (i < NGP) values(i, a);
             if (active)
                 pair_publish_part<L, SPIN, T_LO, T_HI>(D + (wave * B::UNITS + u) * B::DSP, sub, Q0, Q1, Q2, zslot);
             __syncthreads();
-#pragma unroll
-            for (int gi = 0; gi < P::NG; ++gi) {
-                if (B::part_of_t(P::t_of(gi)) != k || own.owner[gi] != wave) continue;
-                const int t = P::t_of(gi), kind = P::kind_of(gi);
-                int tab_base = Y.e0c, blk = SPIN ? BO : 0;
-                if (kind == 1) tab_base = Y.e1p, blk = 2 * BO;
-                if (kind == 2) tab_base = Y.e1m, blk = 0;
-                if (kind == 3) tab_base = Y.e1z, blk = sub ? 0 : 2 * BO;
-                float acc[L + 1];
-#pragma unroll
-                for (int l = 0; l <= L; ++l) acc[l] = 0.f;
 #pragma unroll 1
-                for (int jj = 0; jj < nw; ++jj) {
-                    const float d = D[(jj * B::UNITS + u) * B::DSP + P::slot(gi) - B::sbase(T_LO) + sub];
-                    const float* te = tab + Y.glob + (r * W + (SPLIT ? jj % nr : jj)) * Y.pb;
+            for (; i < NGP; i += W) {
+                if (i + W < NGP) values(i + W, an);
+                const Group G = group(i);
+                const int slot = (G.t == 0 ? (G.kind == 0 ? 0 : 2) : P::T0 + P::PER_T * (G.t - 1) + 2 * G.kind) -
+                                 B::sbase(T_LO);
+                // all reads of a kind together, so that each LDS latency is met once per group:
+                // [m] m3 = +t, -t; [h] units 0..15, 16..31
+                float bv[2][2][2];
+                v4fe acc[2][2];
 #pragma unroll
-                    for (int l = P::lmin(gi); l <= L; ++l)
-                        acc[l] = fmaf(te[kind == 3 ? tab_base + l : tab_base + tri(L, t, l)], d, acc[l]);
-                }
-                if (valid && !(t == 0 && kind == 0 && sub)) {
-                    float* yrow = B::OUT_LDS ? YT + u * B::STO : orow;
+                for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int l = P::lmin(gi); l <= L; ++l) {
-                        float* o = yrow + blk + l * l + l + (sub ? -t : t);
-                        *o = (r == 0) ? acc[l] : *o + acc[l];
+                    for (int h = 0; h < 2; ++h) {
+                        const float* d = D + (lq * B::UNITS + 16 * h + lr) * B::DSP + slot + m;
+                        bv[m][h][0] = lq < nw ? d[0] : 0.f;
+                        bv[m][h][1] = 4 + lq < nw ? d[4 * B::UNITS * B::DSP] : 0.f;
                     }
+                const bool both = G.t > 0 || G.kind == 3;
+                float* yrow[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    yrow[m] = YT + lr * B::STO + (m ? -G.t : G.t) +
+                              (G.kind == 0 ? (SPIN ? BO : 0) : (G.kind == 1 ? 2 * BO : (G.kind == 2 || m ? 0 : 2 * BO)));
+                float old[2][2][4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int l = G.lmin + 4 * lq + c;
+                    const bool in = r > 0 && l <= L;
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            old[m][h][c] = in && (m == 0 || both) ? yrow[m][16 * h * B::STO + l * l + l] : 0.f;
                 }
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        acc[m][h] = v4fe{0.f, 0.f, 0.f, 0.f};
+                        acc[m][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], bv[m][h][0], acc[m][h], 0, 0, 0);
+                        if (nw > 4)
+                            acc[m][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], bv[m][h][1], acc[m][h], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int l = G.lmin + 4 * lq + c;
+                    const bool in = l <= L && !(EXTRA && i == 0 && l == 16);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            if (in && (m == 0 || both)) yrow[m][16 * h * B::STO + l * l + l] = old[m][h][c] + acc[m][h][c];
+                }
+                a[0] = an[0];
+                a[1] = an[1];
             }
             __syncthreads();
         };
@@ -724,26 +846,20 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
         if constexpr (K > 2) part(std::integral_constant<int, 2>{});
         if constexpr (K > 3) part(std::integral_constant<int, 3>{});
     }
-    if constexpr (B::OUT_LDS) {
-        if constexpr (PAR) {
-            parity_mix_rows<L>(YT, B::STO, nvalid, true, tid, B::THREADS);
-            __syncthreads();
+    if constexpr (PAR) {
+        parity_mix_rows<L>(YT, B::STO, nvalid, true, tid, B::THREADS);
+        __syncthreads();
+    }
+    if constexpr (!PAD) {
+        store_tile<B::NC, B::STO>(out + u0 * B::NC, nvalid, YT, tid, B::THREADS);
+    } else {  // slots of degree <= Lout of each spin block
+        const int nco = B::NS * bbo;
+        for (int i = tid; i < nvalid * nco; i += B::THREADS) {
+            const int uu = i / nco, rem = i - uu * nco, b = rem / bbo, q = rem - b * bbo;
+            const float v = YT[uu * B::STO + b * B::BB + q];
+            if constexpr (F32) out[(u0 + uu) * nco + rem] = v;
+            else out[(u0 + uu) * nco + rem] = f32_to_bf16(v);
         }
-        if constexpr (!PAD) {
-            store_tile<B::NC, B::STO>(out + u0 * B::NC, nvalid, YT, tid, B::THREADS);
-        } else {  // slots of degree <= Lout of each spin block
-            const int nco = B::NS * bbo;
-            for (int i = tid; i < nvalid * nco; i += B::THREADS) {
-                const int uu = i / nco, rem = i - uu * nco, b = rem / bbo, q = rem - b * bbo;
-                const float v = YT[uu * B::STO + b * B::BB + q];
-                if constexpr (F32) out[(u0 + uu) * nco + rem] = v;
-                else out[(u0 + uu) * nco + rem] = f32_to_bf16(v);
-            }
-        }
-    } else if constexpr (PAR && F32) {
-        // the rows were accumulated in global memory by several waves; the barrier
-        // that ends the last round orders those stores before these reads
-        parity_mix_rows<L>(out + u0 * B::NC, B::NC, nvalid, true, tid, B::THREADS);
     }
 }
 

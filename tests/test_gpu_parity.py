@@ -208,6 +208,28 @@ def test_parity_basis_large_degree(L):
     run_and_compare(L, L, L, S3, 37, 3, "fp32", 2, seed=100 + L)
 
 
+@pytest.mark.parametrize("L,basis,spins,N", [(9, 0, S3, 1), (9, 2, S3, 33), (11, 0, (0,), 31), (12, 2, S3, 65),
+                                             (15, 0, S3, 32), (16, 0, S3, 33), (16, 2, (-1, 0, 1), 17),
+                                             (16, 0, (0,), 33)])
+def test_large_degree_projection_edges(L, basis, spins, N):
+    """The projection of the large-degree kernel contracts each group's nodes on the matrix units: 17 orders
+    (L = 16, t = 0) and a last round of 1 to 8 records, units up to and past a 16-unit column tile.  Small inputs
+    (products below the normal range of fp32) keep their subnormal digits.  A unit's error is that of sums of
+    (L + 1)^2 terms in fp32, far under 1e-5; in the subnormal run the spacing 2^-149 bounds it further."""
+    run_and_compare(L, L, L, spins, N, 1, "fp32", basis, seed=700 + L + N)
+    if basis == 2 or spins == (0,):
+        return
+    x1 = workloads.draw(L, N, 1, 41, "fp32", spins, "unit", "cuda") * 2.0 ** -60
+    x2 = workloads.draw(L, N, 1, 42, "fp32", spins, "unit", "cuda") * 2.0 ** -60
+    plan = Plan(L, L, L, spins, "fp32", basis)
+    big, small = plan.forward(x1, x2), plan.forward(x1 * 2.0 ** -5, x2 * 2.0 ** -5)
+    assert torch.isfinite(small).all() and (small != 0).any()
+    # each of the NT rounds' additions and of the final sums may round once to a multiple of 2^-149, weighted
+    # by table values of a few units: (3 L + 3) / 2 nodes times (2 L + 1) orders, times 8
+    bound = 8 * (3 * L + 3) * (2 * L + 1) * 2.0 ** -149
+    assert float((small.double() - big.double() * 2.0 ** -10).abs().max()) <= bound
+
+
 def test_parity_basis_scalar_spin_large_degree():
     # no |s| = 1 sector: the paper-basis kernel serves the parity plan
     run_and_compare(9, 9, 9, (0,), 29, 5, "fp32", 2, seed=109)
