@@ -12,7 +12,7 @@ LIB = os.path.join(PKG, "libspingtp.so")
 SOURCES = ["plan.cpp", "api.cpp", "forward.hip", "forward_big_parity.hip", "forward_big_padded.hip",
            "forward_big_parity_padded.hip", "forward_mfma.hip", "forward_pre.hip",
            "forward_pre_large.hip", "forward_pre_weighted.hip", "forward_direct.hip", "backward.hip", "backward_v1w.hip", "forward_uvw.hip",
-           "uvw_blocks.hip", "channel_blocks.hip", "direct_unrolled_paper.hip", "direct_unrolled_paired.hip", "direct_unrolled_parity.hip"]
+           "uvw_blocks.hip", "channel_blocks.hip", "gram_x2.hip", "direct_unrolled_paper.hip", "direct_unrolled_paired.hip", "direct_unrolled_parity.hip"]
 # per-source additions
 # the compile-time tensor patterns take more constant-evaluation steps than the default limit
 _CONSTEXPR = ["-fconstexpr-steps=200000000"]

@@ -131,6 +131,16 @@ int64_t row_length(const spingtp_plan_s* p) {
     return static_cast<int64_t>(p->n_spins) * (p->L2 + 1) * (p->L2 + 1);
 }
 
+// grad_x2 from the edges' Gram matrices (gram_x2.hip) from 8 channels on: its cost per edge has a
+// fixed part (the tensor's entries) that fewer channels do not earn back, and a chain over the
+// channels that is short against the sum over per-channel rows.  fp32, us, per-channel products
+// -> Gram: 65,536 edges x 1 channel 8.6 -> 16 (L = 1), 15 -> 35 (L = 2), 27 -> 94 (L = 3); x 8
+// channels 29 -> 21, 60 -> 40, 142 -> 103; 8,192 edges x 100 channels 67 -> 15, 107 -> 30,
+// 220 -> 69; one edge x 16,384 channels 2,739 -> 213, 4,904 -> 532, 5,568 -> 1,613.
+bool use_gram(const spingtp_plan_s* p, int64_t C) {
+    return p->d_gram != nullptr && C >= 8;
+}
+
 }  // namespace
 
 extern "C" spingtp_status spingtp_backward_v1_workspace_size(spingtp_plan plan, int64_t N, int64_t C,
@@ -183,6 +193,17 @@ extern "C" spingtp_status spingtp_backward_v1(spingtp_plan plan, const void* x1,
     }
     if (grad_x2 != nullptr) {
         if (workspace == nullptr || misaligned(workspace) || workspace_bytes < need) return SPINGTP_ERR_INVALID_ARG;
+        if (use_gram(plan, C)) {
+            if (x1 == nullptr || grad_out == nullptr || misaligned(x1) || misaligned(grad_out))
+                return SPINGTP_ERR_INVALID_ARG;
+            int cur = -1;
+            if (hipGetDevice(&cur) != hipSuccess) return SPINGTP_ERR_HIP;
+            if (cur != plan->device) return SPINGTP_ERR_INVALID_ARG;
+            return spingtp::launch_gram_x2(plan->dtype, x1, grad_out, grad_x2, N, C,
+                                           static_cast<int>(row_length(plan)), plan->d_gram, s) == hipSuccess
+                       ? SPINGTP_OK
+                       : SPINGTP_ERR_HIP;
+        }
         const spingtp_status r =
             plan->d_tab_bwd != nullptr
                 ? spingtp::run_forward(plan, plan->kernel, grad_out, x1, workspace, N, C, false, stream,

@@ -70,6 +70,19 @@ const KernelEntry* find_direct_kernel(int lds_floats, int dtype);
 void build_direct_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags, int role,
                         std::vector<uint32_t>& out, int* lds_floats, const std::vector<double>* dense = nullptr);
 
+// grad_x2 of the product with x2 shared by the channels (gram_x2.hip), for one degree on all three
+// sides and rows of nc <= kGramMaxNC slots.  Table words: items per thread, word offset of the
+// items, then nc + 1 thread numbers (output slot k2 is summed by the threads [w[k2], w[k2 + 1])),
+// then items [item][thread] of two words: index s(k1) R + s(k3) of the Gram element, R = nc
+// rounded up to 16 and s(k) the slot's place in the kernel's tiles (padding: R R, a zero), and
+// the tensor's value.  T: the dense tensor.
+constexpr int kGramThreads = 256;
+constexpr int kGramMaxNC = 48;
+void build_gram_table(int nc, const std::vector<double>& T, std::vector<uint32_t>& out);
+// dtype: spingtp_dtype.  x1, g [N][C][nc], gx2 [N][nc].
+hipError_t launch_gram_x2(int dtype, const void* x1, const void* g, void* gx2, int64_t N, int64_t C, int nc,
+                          const uint32_t* tab, hipStream_t stream);
+
 // The direct kernel unrolled over the tensor's entries (direct_unrolled.h), spins {-2..2} at
 // L1 = L2 = Lout = L <= 2: per role its entries in order and its launch, whose `val` holds one
 // fp32 value per entry (device).  nullptr where none is built.
@@ -358,6 +371,7 @@ struct spingtp_plan_s {
     uint32_t* d_aux;  // matrix-core operand tables, nullptr for the vector-ALU kernels
     uint32_t* d_pre;  // sparse tensor of the precontracted kernel, nullptr if not used
     uint32_t* d_pre_bwd;  // the same with J x2 (spingtp_backward_v1), nullptr if not used
+    const uint32_t* d_gram;  // table of the Gram kernel (grad_x2, x2 shared), in d_pre_bwd; nullptr if none
     uint32_t* d_pre_w;    // the per-channel path-weighted table (SPINGTP_CHANNEL_WEIGHTS), nullptr if not built
     const spingtp::KernelEntry* kernel_v1w;  // its kernel (spingtp_forward_v1_weighted)
     uint32_t* d_bw1w;  // entry lists of spingtp_backward_v1_weighted, nullptr if not built

@@ -1343,6 +1343,55 @@ bool build_uvw_table(int L1, int L2, int LO, const int* spins, int n_spins, unsi
     return true;
 }
 
+void build_gram_table(int nc, const std::vector<double>& T, std::vector<uint32_t>& out) {
+    const int nt = (nc + 15) / 16, R = 16 * nt;
+    // column k of a row is tile i of lane l: the lane reads nt columns from min(nt l, nc - nt)
+    auto slot = [&](int k) {
+        const int l = k / nt;
+        return 16 * (k - std::min(nt * l, nc - nt)) + l;
+    };
+    std::vector<std::vector<std::pair<uint32_t, float>>> lists(nc);
+    for (int k1 = 0; k1 < nc; ++k1)
+        for (int k2 = 0; k2 < nc; ++k2)
+            for (int k3 = 0; k3 < nc; ++k3) {
+                const double v = T[(static_cast<size_t>(k1) * nc + k2) * nc + k3];
+                if (std::fabs(v) > 1e-12)  // the rest is quadrature round-off of exact zeros
+                    lists[k2].emplace_back(static_cast<uint32_t>(slot(k1) * R + slot(k3)), static_cast<float>(v));
+            }
+    // threads per output: one for each that has entries, then the rest where a thread has most to do
+    std::vector<int> threads(nc);
+    int left = kGramThreads;
+    for (int k = 0; k < nc; ++k) left -= threads[k] = lists[k].empty() ? 0 : 1;
+    auto share = [&](int k) { return threads[k] == 0 ? 0 : (static_cast<int>(lists[k].size()) + threads[k] - 1) / threads[k]; };
+    for (; left > 0; --left) {
+        int best = 0;
+        for (int k = 1; k < nc; ++k)
+            if (share(k) > share(best)) best = k;
+        if (share(best) <= 4) break;  // the items come in fours
+        ++threads[best];
+    }
+    int ipt = 0;
+    for (int k = 0; k < nc; ++k) ipt = std::max(ipt, share(k));
+    ipt = (ipt + 3) / 4 * 4;
+    const int at = (2 + nc + 1 + 15) / 16 * 16;
+    out.assign(static_cast<size_t>(at) + 2ull * kGramThreads * ipt, 0u);
+    out[0] = static_cast<uint32_t>(ipt);
+    out[1] = static_cast<uint32_t>(at);
+    for (int i = 0; i < kGramThreads * ipt; ++i) out[at + 2 * i] = static_cast<uint32_t>(R * R);
+    int t = 0;
+    for (int k = 0; k < nc; ++k) {
+        out[2 + k] = static_cast<uint32_t>(t);
+        const size_t n = lists[k].size();
+        for (int j = 0; j < threads[k]; ++j, ++t)
+            for (size_t e = n * j / threads[k], i = 0; e < n * (j + 1) / threads[k]; ++e, ++i) {
+                uint32_t* w = &out[at + 2 * (i * kGramThreads + t)];
+                w[0] = lists[k][e].first;
+                std::memcpy(&w[1], &lists[k][e].second, 4);
+            }
+    }
+    out[2 + nc] = static_cast<uint32_t>(t);
+}
+
 void build_direct_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags, int role,
                         std::vector<uint32_t>& out, int* lds_floats, const std::vector<double>* dense) {
     std::vector<double> own;
@@ -1646,6 +1695,7 @@ struct PlanHost {
     std::vector<double> tab, tab_bwd;
     std::vector<uint32_t> aux, pre, pre_bwd, dir, dir_b1, dir_b2, pre_w, bw1w, uvw;
     size_t cw_off = 0, uvwz_off = 0;  // first word of the block kernels' tables in bw1w and uvw (0: none)
+    size_t gram_off = 0;              // first word of the Gram kernel's table in pre_bwd (0: none)
     size_t uvw_off[3] = {0, 0, 0};  // first word of each role's table in uvw
     bool padded = false;            // mixed degrees on the large-degree kernel (aux: 3 degree triples)
     spingtp::Bw1wShape bw1w_shape{};
@@ -1843,14 +1893,21 @@ spingtp_status build_plan_host(int L1, int L2, int Lout, const int* spins, int n
                 spingtp::uvwz_fits(h.uvwz_shape))
                 h.uvwz_off = append_table(h.uvw, uvwz);
         }
-        if (kv1->family == 5 &&
-            !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre, false, weighted ? &dense : nullptr))
+        if (kv1->family == 5 && dense.empty())
+            spingtp::build_dense_tensor(L1, L2, Lout, spins, n_spins, basis, dense);
+        if (kv1->family == 5 && !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre, false, &dense))
             return SPINGTP_ERR_INTERNAL;
         // spingtp_backward_v1 on the precontracted kernel: the same table with J x2 (the
         // conjugation identity holds for the unweighted tensor only)
         if (kv1->family == 5 && L1 == L2 && L2 == Lout && !weighted &&
-            !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre_bwd, true))
+            !spingtp::build_pre_tables(L1, L2, Lout, spins, n_spins, basis, pre_bwd, true, &dense))
             pre_bwd.clear();
+        const int nc = n_spins * (L1 + 1) * (L1 + 1);
+        if (!pre_bwd.empty() && fourier_bwd && nc <= spingtp::kGramMaxNC) {
+            std::vector<uint32_t> gram;
+            spingtp::build_gram_table(nc, dense, gram);
+            h.gram_off = append_table(pre_bwd, gram);
+        }
         // spingtp_backward: square plans with a forward kernel, input 2 conjugated
         if (fourier_bwd && spingtp::build_tables(L1, L2, Lout, spin_mode, basis, tab_bwd, true)) {
             has_backward = true;
@@ -1963,6 +2020,7 @@ static spingtp_status create_plan(int L1, int L2, int Lout, const int* spins, in
     p->d_aux = d.aux;
     p->d_pre = d.pre;
     p->d_pre_bwd = d.pre_bwd;
+    p->d_gram = h.gram_off != 0 ? d.pre_bwd + h.gram_off : nullptr;
     p->d_tab_bwd = h.has_backward ? (h.same_bwd ? d.tab : d.tab_bwd) : nullptr;
     p->own_tab_bwd = d.tab_bwd != nullptr;
     p->d_dir = d.dir;

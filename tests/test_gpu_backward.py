@@ -222,6 +222,39 @@ def test_backward_v1_scalar_spin_and_bf16(L):
     run_backward_v1(L, S3, 9, 20, "bf16", 0, seed=L + 1)
 
 
+@pytest.mark.parametrize("L,spins,N,C,dtype,basis", [
+    (1, S3, 5, 8, "fp32", 0), (1, S3, 1, 33, "fp32", 2), (2, S3, 4, 15, "fp32", 0), (2, S3, 3, 100, "bf16", 2),
+    (3, S3, 5, 16, "fp32", 1), (3, S3, 2, 9, "bf16", 0), (3, S3, 1, 300, "fp32", 0), (3, S3, 6, 7, "fp32", 0),
+    (0, S3, 4, 8, "fp32", 0), (3, (0,), 9, 31, "fp32", 0), (4, (0,), 7, 17, "fp32", 0)])
+def test_backward_v1_gram_edges(L, spins, N, C, dtype, basis):
+    """grad_x2 through the edge's Gram matrix: remainders of the 16-channel steps and of the 4 edges of a
+    workgroup, rows of 3 to 48 slots, one channel short of the rule, NaN in the slots with l < |s| and right
+    after the operands.  fp32: each of a slot's entries is a chain over C / 4 steps, then some 100 entries are
+    added, so the relative error is about sqrt(C / 4 + 100) 2^-24 < 1e-6 (C = 300) of the typical sum; the bar
+    leaves a factor 2."""
+    n = len(spins) * (L + 1) ** 2
+    lead = torch.full((2, N * C + 4, n), float("nan"), device="cuda").to(torch.float32 if dtype == "fp32" else torch.bfloat16)
+    valid = torch.as_tensor(valid_mask(spins, L), device="cuda")
+    ops = []
+    for i in range(2):
+        v = workloads.draw(L, N, C, 850 + 10 * L + i, dtype, spins, "unit", "cuda").view(N * C, n)
+        lead[i, : N * C] = torch.where(valid, v, torch.full_like(v, float("nan")))
+        ops.append(lead[i, : N * C].view(N, C, len(spins), (L + 1) ** 2))
+    if ops[1].data_ptr() % 16:
+        ops[1] = ops[1].clone()
+    x2 = workloads.draw(L, N, 1, 870 + L, dtype, spins, "unit", "cuda")
+    plan = Plan(L, L, L, spins, dtype, basis)
+    _, gx2 = plan.backward_v1(ops[0], x2, ops[1])
+    torch.cuda.synchronize()
+    a, c = (torch.nan_to_num(t.double()).view(N * C, n).cpu().numpy() for t in ops)
+    b = np.repeat(x2.view(N, n).double().cpu().numpy(), C, axis=0)
+    _, r2 = oracle.RealGauntTensor(L, L, L, spins, basis).vjp(a, b, c)
+    r2 = r2.reshape(N, C, n).sum(axis=1)
+    got = gx2.view(N, n).double().cpu().numpy()
+    assert np.isfinite(got).all() and (got[:, ~valid.cpu().numpy()] == 0).all()
+    assert rel_l2(got, r2) <= (2e-6 if dtype == "fp32" else 4e-3)  # bf16: the rounding of the result, 2^-8
+
+
 def test_backward_v1_rules():
     L = 2
     N, C = 5, 6
