@@ -219,7 +219,10 @@ spingtp_status spingtp_forward_v1(spingtp_plan plan, const void* x1, const void*
  *   weights: device fp32 [C][n_paths], 4-byte aligned, read only.
  *   x1, x2, out, N, C, stream: as spingtp_forward_v1.
  * Needs a plan created with SPINGTP_CHANNEL_WEIGHTS (else SPINGTP_ERR_UNSUPPORTED).
- * Route: the entry-list kernel of spingtp_forward_weighted with the x2 row shared
+ * Route: for degrees <= 3 and tensors of 256 nonzeros or more the block kernel, which
+ * contracts the tensor with x2 once per edge (K_p, dense in a path's (k1, k3)) and
+ * every channel's blocks with K_p; else the entry-list kernel of
+ * spingtp_forward_weighted with the x2 row shared
  * by the tile's channels (four waves per 64-channel tile walk the tensor's nonzeros
  * by output slot; measured faster on the depthwise runtime table's shapes), where
  * the plan's lists hold the shape and the plan was not created with
@@ -315,7 +318,7 @@ spingtp_status spingtp_backward_weighted_workspace_size(spingtp_plan plan, int64
  *   [(L2+1)^2] of the plan's dtype, 16-byte aligned; weights: device fp32 [V][C][n_paths]
  *   (the slice of channel v is the weight layout of spingtp_forward_v1_weighted);
  *   V >= 1.
- * Runs the entry-list kernel of spingtp_forward_v1_weighted on groups of up to four
+ * Runs the block or entry-list kernel of spingtp_forward_v1_weighted on groups of up to four
  * channels v per launch (each tensor entry takes x1[k1] sum_v W_v[p] x2_v[k2]; as many
  * channels as its LDS holds while two workgroups still fit a compute unit), reading
  * the x2 rows of an edge V n_spins (L2+1)^2 elements apart and adding into out after
@@ -388,6 +391,9 @@ spingtp_status spingtp_backward(spingtp_plan plan, const void* x1, const void* x
  * SpinGTP(grad_out[n][c], J x1[n][c]) of the plan's spingtp_forward kernel go to
  * `workspace` ([N][C][n_spins (L2+1)^2], the plan's dtype), then a second kernel
  * sums them over c in order (fp32 sums; bf16 output rounded to nearest even).
+ * On plans whose v1 kernel is the precontracted one, with rows of at most 48 slots and
+ * C >= 8, grad_x2 is formed from the edge's sums of x1[k1] grad_out[k3] over the channels
+ * (fp32 throughout, one rounding for bf16 output); the workspace is not written then.
  * On plans whose gradients run on the direct kernel (see spingtp_backward), both
  * steps use its role tables instead (grad_x1 with x2 read once per edge), except
  * that grad_x1 stays on the precontracted kernel where the plan has its

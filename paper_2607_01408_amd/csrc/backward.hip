@@ -68,7 +68,8 @@ extern "C" spingtp_status spingtp_backward(spingtp_plan plan, const void* x1, co
 //   grad_x1[n,c] = SpinGTP'(g[n,c], J x2[n])                 (x2 shared: the v1 route)
 //   grad_x2[n]   = sum_c SpinGTP''(g[n,c], J x1[n,c])          (per unit, then summed)
 // The per-unit products of grad_x2 go to the caller's workspace [N][C][NC2] and a
-// reduction kernel sums them over the channels in a fixed order.
+// reduction kernel sums them over the channels in a fixed order; with enough channels,
+// and short rows, the channels are summed before the tensor is applied (gram_x2.hip).
 // ---------------------------------------------------------------------------
 namespace {
 
