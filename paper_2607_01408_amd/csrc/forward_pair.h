@@ -408,15 +408,15 @@ __device__ __forceinline__ void pair_publish(float* D, int sub, const float (&Q0
 // (written in round 0, then read, added and written by the same lane in the same
 // order: deterministic) and leave in one coalesced store.
 //
-// Step (E) from L = 11 on (big_matrix_projection) contracts the round's nodes of each output group (t, kind): a matrix
-// product with the orders l of the group as rows, the records of the round as the
-// contraction and the units as columns, on v_mfma_f32_16x16x4f32 (two of them cover
-// 8 records; the result is bit for bit that of the chain of FMAs over the records).
-// A group's cost is then the same whatever its number of orders, so the groups go
-// round the waves by index.  With one lane per output order of a unit and the
-// groups unrolled under a branch per wave, it took 27% of the kernel at L = 12: the
-// code of all groups passed through the instruction cache in every round, and each
-// spectrum value was read by every order's lane.
+// From L = 11 on (big_matrix_projection) step (E) contracts the round's nodes of each
+// output group (t, kind) as a matrix product, the orders l of the group as rows, the
+// records of the round as the contraction and the units as columns, on
+// v_mfma_f32_16x16x4f32 (two of them cover 8 records; the result is bit for bit that of
+// the chain of FMAs over the records).  A group's cost is then the same whatever its
+// number of orders, so the groups go round the waves by index.  On owner waves, with the
+// groups unrolled under a branch per wave, it took 27% of the kernel at L = 12: the code of
+// all groups passed through the instruction cache in every round, and a record's scalar
+// table loads and LDS read were waited for before the next record's.
 //
 // Bound by the vector units (steps A, C, D) with one workgroup of W waves per CU (the
 // LDS tile allows no second one).  262,144 units, fp32, paper basis, before -> with
