@@ -216,13 +216,22 @@ extern "C" spingtp_status spingtp_forward_depthwise(spingtp_plan plan, const voi
     // up to kFwdCwMaxNv channels per launch, as many as the LDS holds without fewer
     // workgroups per CU than one channel gets (at least two); later launches add
     // into out, in channel order
-    const bool blocks = use_blocks(plan, 1);
-    auto lds = [&](int nv) {
-        return blocks ? spingtp::cw_fwd_lds_floats(plan->cw, nv) : spingtp::fwd_cw_lds_floats(plan->bw1w, nv);
+    const auto channels = [](auto lds) {
+        const int per_cu1 = std::min(2, spingtp::kBw1wMaxLdsFloats / std::max(lds(1), 1));
+        int nv = 1;
+        while (nv < spingtp::kFwdCwMaxNv && spingtp::kBw1wMaxLdsFloats / lds(nv + 1) >= per_cu1) ++nv;
+        return nv;
     };
-    const int per_cu1 = std::min(2, spingtp::kBw1wMaxLdsFloats / std::max(lds(1), 1));
-    int nv_max = 1;
-    while (nv_max < spingtp::kFwdCwMaxNv && spingtp::kBw1wMaxLdsFloats / lds(nv_max + 1) >= per_cu1) ++nv_max;
+    int nv_max = channels([&](int nv) { return spingtp::fwd_cw_lds_floats(plan->bw1w, nv); });
+    bool blocks = use_blocks(plan, 1);
+    if (blocks) {
+        const int nv = channels([&](int n) { return spingtp::cw_fwd_lds_floats(plan->cw, n); });
+        // bf16 rounds out at every launch, so the block kernels (K takes LDS beside the weights)
+        // must not need more of them than the entry lists
+        const int lists = static_cast<int>(std::min<int64_t>(nv_max, V));
+        if (plan->dtype == SPINGTP_FP32 || nv >= lists) nv_max = nv;
+        else blocks = use_blocks(plan, lists);
+    }
     const int dt = plan->dtype == SPINGTP_FP32 ? 0 : 1;
     const hipStream_t st = static_cast<hipStream_t>(stream);
     for (int64_t v = 0; v < V;) {

@@ -452,7 +452,7 @@ def run_depthwise(L1, L2, LO, spins, N, C, V, basis=0, dtype="fp32", seed=0):
     return plan, (x1, x2, W, g), (y, gx1, gx2, gW)
 
 
-# V = 2..4 run as one launch of the fused kernel, V = 5, 6 as four channels and then the rest
+# a launch takes up to four second-input channels, as many as its LDS holds; the rest are added by later ones
 @pytest.mark.parametrize("shape,C,V,basis", [((1, 1, 1), 16, 3, 0), ((2, 2, 2), 70, 2, 2), ((1, 3, 3), 33, 4, 0),
                                              ((2, 1, 2), 64, 2, 1), ((2, 2, 2), 40, 6, 0), ((1, 2, 2), 24, 5, 2)])
 def test_depthwise_shapes(shape, C, V, basis):
@@ -499,3 +499,30 @@ def test_channel_block_kernel_edges(L1, L2, LO, spins, N, C, V, basis, dtype):
     if V == 1:
         run_channel_weighted(L1, L2, LO, spins, N, C, basis, dtype, seed=C)
         run_channel_weighted_backward(L1, L2, LO, spins, N, C, basis, dtype, seed=C)
+
+
+@pytest.mark.parametrize("shape,spins,basis,launches", [
+    ((2, 2, 2), S3, 0, (2,)), ((2, 2, 2), S3, 2, (3,)), ((1, 3, 3), S3, 2, (4,)), ((1, 2, 2), S3, 0, (4,)),
+    ((1, 3, 3), S3, 2, (4, 2)), ((2, 2, 2), S3, 0, (2, 2, 2)),
+    ((2, 2, 2), S5, 0, (2,))])  # the block kernel's LDS holds one channel: the entry lists
+def test_depthwise_bf16_roundings(shape, spins, basis, launches):
+    """The bf16 depthwise output is rounded once per launch.  `launches`: the channels v of each.  The
+    roundings are independent and each is as large as one rounding of the sum so far, whose share of the
+    result's variance is the share of v summed (inputs and weights of one distribution), so the error is
+    sqrt(sum of the shares) times that of one rounding of the exact result.  6% for the spread over the
+    10^5 values and the unequal paths; one launch more would give 10 to 29%."""
+    N, C, V = 40, 64, sum(launches)
+    rng = np.random.default_rng(7 + V)
+    W = torch.as_tensor(rng.standard_normal((V, C, len(paths_host(*shape, spins, basis)))), dtype=torch.float32,
+                        device="cuda")
+    x1 = workloads.draw(shape[0], N, C, 95, "bf16", spins, "unit", "cuda")
+    x2 = workloads.draw(shape[1], N, V, 96, "bf16", spins, "unit", "cuda")
+    y = Plan(*shape, spins, "bf16", basis, channel_weights=True).forward_depthwise(x1, x2, W)
+    torch.cuda.synchronize()
+    ref = oracle.depthwise(host(x1, N * C).reshape(N, C, -1), host(x2, N * V).reshape(N, V, -1),
+                           W.double().cpu().numpy(), *shape, spins, basis).reshape(N * C, -1)
+    once = rel_l2(torch.as_tensor(ref).to(torch.bfloat16).double().numpy(), ref)
+    shares = np.cumsum(launches) / V
+    err = rel_l2(host(y, N * C), ref)
+    print(f"[depthwise] bf16 {shape} V={V} error {err:.3e}, one rounding {once:.3e}", flush=True)
+    assert err <= 1.06 * np.sqrt(shares.sum()) * once
