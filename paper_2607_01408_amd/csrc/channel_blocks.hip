@@ -47,13 +47,6 @@ __device__ __forceinline__ void cw_store(uint16_t* p, float v) { *p = f32_to_bf1
 // floats between the rows of K at one contracted slot
 constexpr __host__ __device__ int cw_k_stride(int d) { return d == 1 ? 1 : (d == 3 ? 4 : 8); }
 
-// a wave's LDS accesses are in order; this keeps the compiler from moving one lane's reads of
-// another lane's writes across
-__device__ __forceinline__ void cw_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // rows [0, nrows) of a contiguous [nrows][nc] block into LDS rows of stride st, eight loads in
 // flight per thread; (r, c) advance by THR elements without a division per element
 template <int THR, typename TIO>
@@ -246,9 +239,9 @@ __device__ __forceinline__ void cw_fwd_block(const uint32_t* __restrict__ blk, c
 #pragma unroll 1
     for (int v = 0; v < NV; ++v) {
         const float* Wv = Wr + v * wv;
-        cw_wave_sync();
+        wave_lds_order();
         cw_form_k(items + blk[3], static_cast<int>(blk[4]), X2 + v * st2, Kt, lane);
-        cw_wave_sync();
+        wave_lds_order();
         cw_fwd_group<DO, 1>(R, 0, e1, Wv, X1r, Kt, out);
         cw_fwd_group<DO, 3>(R, e1, e3, Wv, X1r, Kt, out);
         cw_fwd_group<DO, 5>(R, e3, e5, Wv, X1r, Kt, out);
@@ -380,9 +373,9 @@ __device__ __forceinline__ void cw_bwd_block(const uint32_t* __restrict__ blk, c
     const int e1 = static_cast<int>(blk[5] & 0xffu), e3 = e1 + static_cast<int>((blk[5] >> 8) & 0xffu);
     const int e5 = e3 + static_cast<int>((blk[5] >> 16) & 0xffu), e7 = static_cast<int>(blk[2]);
     const int o = static_cast<int>(blk[0] & 0xffffu);
-    cw_wave_sync();
+    wave_lds_order();
     cw_form_k(items + blk[3], static_cast<int>(blk[4]), X2, Kt, lane);
-    cw_wave_sync();
+    wave_lds_order();
     float x[D1], gx[D1];
 #pragma unroll
     for (int k = 0; k < D1; ++k) {

@@ -55,23 +55,16 @@ __device__ __forceinline__ void entry_chunks(const float (&a)[NA], const float (
     }
 }
 
-// a wave's LDS accesses are in order; this keeps the compiler from moving one lane's reads of
-// another lane's writes across
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // the wave's rows u0 .. u0 + nvalid - 1 through its LDS tile into one register row per lane
 template <int N, typename TIO>
 __device__ __forceinline__ void unrolled_rows(const TIO* __restrict__ src, int nvalid, float* tile, int lane,
                                               float (&dst)[N]) {
     if (nvalid == 64) load_full_tile<N, N | 1, 64, 64>(src, tile, lane);
     else load_tile<N, N | 1>(src, nvalid, tile, lane, 64);
-    wave_lds_sync();
+    wave_lds_order();
 #pragma unroll
     for (int k = 0; k < N; ++k) dst[k] = lane < nvalid ? tile[lane * (N | 1) + k] : 0.f;
-    wave_lds_sync();
+    wave_lds_order();
 }
 
 // dtype (uniform): 0 fp32, 1 bf16 rows (one instantiation for both: the unrolled body is the
@@ -104,7 +97,7 @@ __global__ __launch_bounds__(64 * kUnrolledWaves) void spingtp_fwd_unrolled_kern
     entry_chunks<P, 0>(ra, rb, ro, p, val);
 #pragma unroll
     for (int k = 0; k < N; ++k) tile[lane * (N | 1) + k] = ro[0][k] + ro[1][k];
-    wave_lds_sync();
+    wave_lds_order();
     if (dtype == 0) store_tile<N, N | 1>(static_cast<float*>(out) + u0 * N, nvalid, tile, lane, 64);
     else store_tile<N, N | 1>(static_cast<uint16_t*>(out) + u0 * N, nvalid, tile, lane, 64);
 }

@@ -54,13 +54,6 @@ __device__ __forceinline__ uint16_t from_f32<uint16_t>(float v) {
     return f32_to_bf16(v);
 }
 
-// Orders a wave's LDS accesses across its lanes (LDS executes a wave's
-// instructions in order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Bit 4 s + j is set when x1 slot k1 = 16 s + 4 g + j (MFMA step (s, j) of lane
 // group g) is data: k1 < nc1 and, in its spin block of blk1 slots (spins -S..S in
 // order, so |s| = |b - ns / 2| for block b), degree l >= |s|, i.e. in-block index

@@ -28,14 +28,13 @@
 #include <atomic>
 #include <cstdint>
 
+#include "device_common.h"
 #include "internal.h"
 
 namespace spingtp {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kZE = 16;    // edges of a tile: the N dimension of the 16x16x4 products
 constexpr int kZS = 17;    // LDS stride of one (channel, slot) row of kZE edges
@@ -503,7 +502,7 @@ __device__ __forceinline__ void load_row(const float* __restrict__ p, float (&v)
 }
 
 // grad_W.  A workgroup owns up to kUvwzUnitPaths paths of one (rho1, rho3) pair, 32 channels
-// u, 32 channels w and one v; wave i takes the edges 8 (i + 8 t) .. + 7 of turn t, and
+// u, 32 channels w and one v; wave i takes the edges 8 (i + 16 t) .. + 7 of turn t, and
 // nothing is shared between the waves until their sums are added, in wave order, at the end
 // (so no barrier in the loop).  A lane holds channel u = w = lane % 32 of one edge of a pair:
 // the operand R[u] = sum_k1 x1[u, k1] K[k1, k3] of the product is formed in registers from
@@ -559,18 +558,20 @@ __device__ __forceinline__ void grad_w_unit(const GradWArgs& P, const uint32_t* 
     const int64_t n_first = kGE * wave;
     fetch(n_first + half, xv[0], gv[0]);
     for (int64_t n0 = n_first; n0 < P.N; n0 += kGE * kGWaves) {
-        // this turn's K (the wave's own LDS region: the wave's accesses are in order)
+        // this turn's K, in the wave's own LDS region: the last turn's reads of K and x2 are
+        // ordered before these writes, the x2 rows before the lanes that form K, K before its use
+        wave_lds_order();
         for (int i = lane; i < kGE * stx; i += 64) {
             const int e = i / stx, k = i - e * stx;
             XB[i] = (k < P.nc2 && n0 + e < P.N) ? P.x2[((n0 + e) * P.V + v) * P.nc2 + k] : 0.f;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         for (int i = lane >> 3; i < np * PER; i += 8) {
             const int j = i / PER, rem = i - j * PER, k1 = rem / D3, k3 = rem - k1 * D3;
             const int e = lane & 7;
             Kt[((j * D3 + k3) * kGE + e) * KD + k1] = contract_record(R[i], XB + e * stx);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
 #pragma unroll
         for (int s = 0; s < kGE / 2; ++s) {
             const int e = 2 * s + half;
