@@ -533,10 +533,10 @@ namespace {
 bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
 
 // Blocks up to 7 slots wide: the kernels that contract the tensor with x2 first
-// (uvw_blocks.hip); their weight offsets within a path are 32-bit, and the second-input
-// channels a grid dimension.
-bool use_blocks(spingtp_plan plan, int64_t U, int64_t V, int64_t W) {
-    return plan->d_uvwz != nullptr && V <= 4096 && U * V * W < (int64_t{1} << 29);
+// (uvw_blocks.hip); their weight offsets within a path are 32-bit, the second-input channels
+// a grid dimension, and 16 edges take 512 threads (a grid holds 2^32).
+bool use_blocks(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W) {
+    return plan->d_uvwz != nullptr && V <= 4096 && U * V * W < (int64_t{1} << 29) && N < (int64_t{1} << 26);
 }
 
 // Forward and grad_x1 there run one channel product per v over the `a` input channels, so
@@ -544,8 +544,8 @@ bool use_blocks(spingtp_plan plan, int64_t U, int64_t V, int64_t W) {
 // matrix cores.  Measured at (2, 2, 2), 512 edges: 37 us per v against 120 us per 32 pairs
 // (a = 2, v = 32: 1,190 against 241 us; a = 16, v = 32: 1,157 against 2,003; a = 16, v = 8 at
 // 256 edges: 312 against 470; v = 1: 2-4x faster at every a).
-bool use_blocks_mix(spingtp_plan plan, int64_t U, int64_t V, int64_t W, int64_t a) {
-    return use_blocks(plan, U, V, W) && V <= 3 * ((a * V + 31) / 32);
+bool use_blocks_mix(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W, int64_t a) {
+    return use_blocks(plan, N, U, V, W) && V <= 3 * ((a * V + 31) / 32);
 }
 
 }  // namespace
@@ -568,7 +568,7 @@ extern "C" spingtp_status spingtp_forward_fully_connected(spingtp_plan plan, con
     if (cur != plan->device) return SPINGTP_ERR_INVALID_ARG;
     const int u = static_cast<int>(U), v = static_cast<int>(V), w = static_cast<int>(W);
     const hipError_t e =
-        use_blocks_mix(plan, U, V, W, U)
+        use_blocks_mix(plan, N, U, V, W, U)
             ? spingtp::launch_uvwz_mix(static_cast<const float*>(x1), static_cast<const float*>(x2), weights,
                                        static_cast<float*>(out), N, u, v, w, V * W, W, 1, U * V * W, plan->uvwz,
                                        plan->d_uvwz, 0, static_cast<hipStream_t>(stream))
@@ -618,14 +618,14 @@ extern "C" spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, co
     const int u = static_cast<int>(U), v = static_cast<int>(V), w = static_cast<int>(W);
     const int64_t ps = U * V * W;
     hipError_t e = hipSuccess;
-    if (want1 && use_blocks_mix(plan, U, V, W, W))
+    if (want1 && use_blocks_mix(plan, N, U, V, W, W))
         e = spingtp::launch_uvwz_mix(g, a2, weights, static_cast<float*>(grad_x1), N, w, v, u, 1, W, V * W, ps,
                                      plan->uvwz, plan->d_uvwz, 1, s);
     else if (want1)  // pairs (v, w) of x2 and grad_out, output channels u
         e = spingtp::launch_uvw_mix(a2, g, weights, static_cast<float*>(grad_x1), N, v, w, u, W, 1, V * W, ps,
                                     plan->d_uvw + plan->uvw_off[1], rows ? plan->uvw_blocks[1] : 0,
                                     plan->uvw_max_d3[1], static_cast<int>(nc1), s);
-    if (e == hipSuccess && want2 && use_blocks(plan, U, V, W))
+    if (e == hipSuccess && want2 && use_blocks(plan, N, U, V, W))
         e = spingtp::launch_uvwz_grad_x2(a1, g, weights, static_cast<float*>(grad_x2), N, u, v, w, plan->uvwz,
                                          plan->d_uvwz, s);
     else if (e == hipSuccess && want2)  // through gR_p = W_p g, then x1 and the entries
@@ -633,7 +633,7 @@ extern "C" spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, co
                                         plan->d_uvw + plan->uvw_off[2], plan->uvw_blocks[2], rows ? plan->uvw_paths : 0,
                                         static_cast<int>(nc1), static_cast<int>(nc2), static_cast<int>(nco),
                                         2 * plan->L1 + 1, 2 * plan->L2 + 1, s);
-    if (e == hipSuccess && wantw && use_blocks(plan, U, V, W))
+    if (e == hipSuccess && wantw && use_blocks(plan, N, U, V, W))
         e = spingtp::launch_uvwz_grad_w(a1, a2, g, grad_weights, N, u, v, w, plan->uvwz, plan->d_uvwz, s);
     else if (e == hipSuccess && wantw)
         e = spingtp::launch_uvw_grad_w(a1, a2, g, grad_weights, N, u, v, w, plan->d_uvw + plan->uvw_off[0],

@@ -262,3 +262,20 @@ def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
     dispatch, forward and the three gradients."""
     run_uvw(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
     run_uvw_backward(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
+
+
+def test_uvw_more_edges_than_a_grid_of_edge_tiles():
+    """2^27 + 5 edges: 16-edge tiles of 512 threads would be more than the 2^32 work-items of a grid."""
+    N = (1 << 27) + 5
+    plan = Plan(0, 0, 0, (0,), "fp32", 0, fully_connected=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x1, x2, g = (torch.randn((N, 1, 1, 1), generator=gen, device="cuda") for _ in range(3))
+    w = torch.full((1, 1, 1, 1), 1.5, device="cuda")
+    y = plan.forward_fully_connected(x1, x2, w)
+    g1, g2, _ = plan.backward_fully_connected(x1, x2, w, g, need=(True, True, False))
+    torch.cuda.synchronize()
+    t = 1.5 / np.sqrt(4 * np.pi)  # the one entry of T, times the weight
+    for got, a, b in ((y, x1, x2), (g1, x2, g), (g2, x1, g)):
+        ref = t * a.double() * b.double()
+        # one product: at most four roundings (T, and a product each with x, the weight and the other input)
+        assert bool(((got.double() - ref).abs() <= 4 * 2.0 ** -24 * ref.abs() + 2.0 ** -149).all())
