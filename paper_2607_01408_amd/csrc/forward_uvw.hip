@@ -42,6 +42,7 @@
 // workgroup and is summed in a fixed order: deterministic, no atomics.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "internal.h"
@@ -548,6 +549,33 @@ bool use_blocks_mix(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t 
     return use_blocks(plan, N, U, V, W) && V <= 3 * ((a * V + 31) / 32);
 }
 
+int64_t parts(int64_t n, int64_t size) { return (n + size - 1) / size; }
+
+// grad_x2: the block kernel, but for degree 0 with few w (K = w), where the launch is all there is:
+// 65,536 edges, U = V = W = 2 60 against 80 us, W = 8 90 against 80.
+bool use_blocks_grad_x2(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W) {
+    return use_blocks(plan, N, U, V, W) &&
+           (plan->uvwz.dmax > 1 || W >= 8 || parts(N, 16) * plan->uvwz.blocks[2] * V <= 576);
+}
+
+// grad_W: the block kernel's tiles are 32 u of one v, the pairwise kernel's 32 pairs (u, v), so
+// with few u and many v the tiles of the former are mostly padding.  Both times in us, as
+// fitted to 3,700 sizes of 11 shapes (33 to 4,096 edges, 1 to 128 channels; 20% off in the
+// mean): a launch, then per edge the longest chain of one workgroup or the chip's throughput,
+// and for the block kernel the sums over its 16 waves per tile.  (3, 3, 3), 1,024 edges,
+// pairwise against blocks: (U, V, W) = (1, 16, 1) 691 against 940, (4, 16, 4) 1,380 against 948,
+// (2, 64, 8) at 512 edges 1,273 against 1,867, (64, 1, 64) 1,939 against 304.
+bool use_blocks_grad_w(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W) {
+    if (!use_blocks(plan, N, U, V, W)) return false;
+    const double n = static_cast<double>(N), np = plan->uvw_paths, work = plan->uvwz.work3;
+    const double tiles = static_cast<double>(V * parts(U, 32) * parts(W, 32)), pairs = static_cast<double>(U * V);
+    const double blocks = 7 + (n + 20) * std::max(0.06, 4e-5 * work * tiles) + (W > 64 ? 0.02 : 0.01) * np * tiles;
+    const double pairwise = 9 + (n + 10) * std::max(0.29 + 0.0096 * std::min(pairs, 32.0),
+                                                    2.2e-4 * np * static_cast<double>(parts(U * V, 32) * parts(W, 128)) +
+                                                        1.1e-5 * work * pairs);
+    return blocks <= pairwise;
+}
+
 }  // namespace
 
 extern "C" spingtp_status spingtp_forward_fully_connected(spingtp_plan plan, const void* x1, const void* x2,
@@ -625,7 +653,7 @@ extern "C" spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, co
         e = spingtp::launch_uvw_mix(a2, g, weights, static_cast<float*>(grad_x1), N, v, w, u, W, 1, V * W, ps,
                                     plan->d_uvw + plan->uvw_off[1], rows ? plan->uvw_blocks[1] : 0,
                                     plan->uvw_max_d3[1], static_cast<int>(nc1), s);
-    if (e == hipSuccess && want2 && use_blocks(plan, N, U, V, W))
+    if (e == hipSuccess && want2 && use_blocks_grad_x2(plan, N, U, V, W))
         e = spingtp::launch_uvwz_grad_x2(a1, g, weights, static_cast<float*>(grad_x2), N, u, v, w, plan->uvwz,
                                          plan->d_uvwz, s);
     else if (e == hipSuccess && want2)  // through gR_p = W_p g, then x1 and the entries
@@ -633,7 +661,7 @@ extern "C" spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, co
                                         plan->d_uvw + plan->uvw_off[2], plan->uvw_blocks[2], rows ? plan->uvw_paths : 0,
                                         static_cast<int>(nc1), static_cast<int>(nc2), static_cast<int>(nco),
                                         2 * plan->L1 + 1, 2 * plan->L2 + 1, s);
-    if (e == hipSuccess && wantw && use_blocks(plan, N, U, V, W))
+    if (e == hipSuccess && wantw && use_blocks_grad_w(plan, N, U, V, W))
         e = spingtp::launch_uvwz_grad_w(a1, a2, g, grad_weights, N, u, v, w, plan->uvwz, plan->d_uvwz, s);
     else if (e == hipSuccess && wantw)
         e = spingtp::launch_uvw_grad_w(a1, a2, g, grad_weights, N, u, v, w, plan->d_uvw + plan->uvw_off[0],

@@ -337,6 +337,7 @@ constexpr int kUvwzMaxD = 7;
 constexpr int kUvwzUnitPaths = 3;
 struct UvwzShape {
     int nc1, nc2, nco, d1max, d2max, d3max, dmax, blocks[3], units;
+    int work3;  // the widths of the paths' output blocks, summed
 };
 // false where a block is wider than kUvwzMaxD
 bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,

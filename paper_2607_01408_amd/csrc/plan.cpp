@@ -1139,6 +1139,7 @@ bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spin
     for (int p = 0; p < np; ++p) {
         const int f1 = first(0, paths[p][0]), f2 = first(1, paths[p][1]), f3 = first(2, paths[p][2]);
         const int d1 = width(0, paths[p][0]), d2 = width(1, paths[p][1]), d3 = width(2, paths[p][2]);
+        s.work3 += d3;
         for (int k1 = 0; k1 < d1; ++k1)
             for (int k3 = 0; k3 < d3; ++k3) {
                 ent[p].emplace_back();

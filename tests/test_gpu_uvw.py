@@ -253,7 +253,7 @@ def test_uvw_backward_bitwise_deterministic():
     (1, 1, 2, S3, 5, 33, 2, 67),     # W not a multiple of 4 (4-byte weight loads), two v
     (3, 3, 3, S3, 9, 20, 1, 12),     # blocks of 7 slots
     (2, 2, 2, S5, 18, 6, 3, 18),     # five spins: invalid blocks of 3 slots, pairs with many paths
-    (2, 2, 2, S3, 20, 2, 40, 3),     # few channels, many v: the pairwise kernel for out, the others new
+    (2, 2, 2, S3, 20, 2, 40, 3),     # few channels, many v: the pairwise kernel for out and grad_W
     (0, 1, 1, S3, 33, 65, 1, 129),   # blocks of one slot
 ])
 def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
@@ -262,6 +262,19 @@ def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
     dispatch, forward and the three gradients."""
     run_uvw(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
     run_uvw_backward(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U)
+
+
+@pytest.mark.parametrize("L1,L2,LO,spins,N,U,V,W", [
+    (0, 0, 0, (0,), 9217, 2, 1, 8),  # degree 0: grad_x2 on the block kernel
+    (0, 0, 0, (0,), 9217, 2, 1, 7),  # and on the pairwise kernel
+    (2, 2, 2, S3, 40, 2, 16, 2),     # weight gradient: pairs (u, v) packed
+    (2, 2, 2, S3, 40, 8, 4, 8),      # or tiles of one v
+])
+def test_uvw_both_routes(L1, L2, LO, spins, N, U, V, W):
+    """Both sides of the rules that choose between the block and the pairwise kernels, forward and gradients."""
+    edges = None if N < 100 else [0, 1, 15, 16, N // 2, N - 17, N - 1]
+    run_uvw(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U, edges=edges)
+    run_uvw_backward(L1, L2, LO, spins, N, U, V, W, 0, seed=N + U, edges=edges)
 
 
 def test_uvw_more_edges_than_a_grid_of_edge_tiles():
