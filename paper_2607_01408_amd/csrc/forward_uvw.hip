@@ -1,6 +1,7 @@
 // Fully connected SpinGTP product (mode uvw of App. E.1; Sec. 3.5 eq. spin_gtp) and its
 // gradients on gfx950: the kernels for blocks of any width, and the entry points, which
-// take the kernels of uvw_blocks.hip for blocks up to 7 slots wide (see use_blocks).
+// take the kernels of uvw_blocks.hip for blocks up to 7 slots wide (see use_blocks_mix and
+// the rules after it).
 //
 // For every path p = (rho1, rho2 -> rho3) the product forms
 //   R_p[n, (u, v), m3] = sum over the entries (k1, k2, m3) of p of T x1[n, u, k1] x2[n, v, k2]
@@ -457,6 +458,17 @@ hipError_t fill_zero(float* out, int64_t total, hipStream_t stream) {
 
 }  // namespace
 
+// One output component per workgroup: each forms R of its own component only, so only
+// the weight reads repeat.  That pays wherever the weights of consecutive output
+// channels are adjacent (so = 1, the forward: 1.6-2.2x faster on the App. E.2 shapes and
+// still 1.6x at 16,384 edges), and for the strided weight reads of the gradient roles
+// only in launches of fewer than kSmallGrid workgroups (measured: B = 1024 1.45x faster,
+// B = 4096 1.24x slower).
+bool uvw_one_component(int64_t N, int64_t O, int n_blocks, int max_d3, int64_t so) {
+    const int64_t tiles = (N + kEdges - 1) / kEdges * ((O + kGroupW - 1) / kGroupW);
+    return so == 1 || tiles * n_blocks * ((max_d3 + kUvwChunk - 1) / kUvwChunk) < kSmallGrid;
+}
+
 hipError_t launch_uvw_mix(const float* xa, const float* xb, const float* w, float* out, int64_t N, int A, int B, int O,
                           int64_t sa, int64_t sb, int64_t so, int64_t ps, const uint32_t* table, int n_blocks,
                           int max_d3, int nco, hipStream_t stream) {
@@ -465,13 +477,7 @@ hipError_t launch_uvw_mix(const float* xa, const float* xb, const float* w, floa
     if (N == 0 || A == 0 || B == 0 || O == 0 || n_blocks == 0) return hipSuccess;
     const int64_t gx = (N + kEdges - 1) / kEdges;
     const int64_t groups = (O + kGroupW - 1) / kGroupW;
-    // One output component per workgroup: each forms R of its own component only, so only
-    // the weight reads repeat.  That pays wherever the weights of consecutive output
-    // channels are adjacent (so = 1, the forward: 1.6-2.2x faster on the App. E.2 shapes and
-    // still 1.6x at 16,384 edges), and for the strided weight reads of the gradient roles
-    // only in launches of fewer than kSmallGrid workgroups (measured: B = 1024 1.45x faster,
-    // B = 4096 1.24x slower).
-    const bool small = so == 1 || gx * n_blocks * groups * ((max_d3 + kUvwChunk - 1) / kUvwChunk) < kSmallGrid;
+    const bool small = uvw_one_component(N, O, n_blocks, max_d3, so);
     const int ch = small ? kSmallChunk : kUvwChunk;
     const int n_chunks = (max_d3 + ch - 1) / ch;
     const int64_t gz = groups * n_chunks;
@@ -540,16 +546,38 @@ bool use_blocks(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W) {
     return plan->d_uvwz != nullptr && V <= 4096 && U * V * W < (int64_t{1} << 29) && N < (int64_t{1} << 26);
 }
 
-// Forward and grad_x1 there run one channel product per v over the `a` input channels, so
-// with a few of those and many v the pairwise kernel's K = a v is the better use of the
-// matrix cores.  Measured at (2, 2, 2), 512 edges: 37 us per v against 120 us per 32 pairs
-// (a = 2, v = 32: 1,190 against 241 us; a = 16, v = 32: 1,157 against 2,003; a = 16, v = 8 at
-// 256 edges: 312 against 470; v = 1: 2-4x faster at every a).
-bool use_blocks_mix(spingtp_plan plan, int64_t N, int64_t U, int64_t V, int64_t W, int64_t a) {
-    return use_blocks(plan, N, U, V, W) && V <= 3 * ((a * V + 31) / 32);
-}
-
 int64_t parts(int64_t n, int64_t size) { return (n + size - 1) / size; }
+
+// Forward (role 0: a = U, o = W) and grad_x1 (role 1: a = W, o = U).  The block kernel runs one
+// product per v with K = the `a` input channels in steps of 16, the pairwise kernel one with
+// K = a v whose cost falls with the pairs, so few channels, many v and launches that fill the
+// chip many times over favour the pairwise kernel, most of all where it owns one output
+// component per workgroup (every forward).  Lines fitted to 9,900 sizes of 18 shapes, paper and
+// parity bases, 16 to 65,536 edges, 1 to 128 channels; us, pairwise against blocks:
+//   (2, 2, 2), V = 1, spins {-1, 0, 1}, forward: 1,024 edges, a = 1 / 8 / 64 51 / 67 / 366 against
+//     41 / 44 / 92; 65,536 edges, a = 1 / 4: 1,247 / 1,860 against 1,933 / 2,009;
+//   (3, 3, 3), spin {0}, a = 2, V = 2, 65,536 edges: forward 415 against 1,888;
+//   grad_x1 there, a = 4 (2), V = 2: 1,940 (1,602) against 1,882 (1,891).
+bool use_blocks_mix(spingtp_plan plan, int role, int64_t N, int64_t U, int64_t V, int64_t W) {
+    const spingtp::UvwzShape& s = plan->uvwz;
+    const int64_t a = role == 0 ? U : W, o = role == 0 ? W : U;
+    if (!use_blocks(plan, N, U, V, W) || V > 3 * parts(a * V, 32)) return false;
+    const int d_out = role == 0 ? s.d3max : s.d1max;
+    if (!spingtp::uvw_one_component(N, o, plan->uvw_blocks[role], plan->uvw_max_d3[role], role == 0 ? 1 : V * W))
+        return V == 1 || a >= (s.dmax == 1 ? 16 : V > 2 ? 8 : s.dmax == 3 || d_out == 7 ? 4 : 2);
+    const double per_block = static_cast<double>(plan->uvw_paths) / s.blocks[role];
+    const bool wide = d_out == 7 && per_block >= 6;  // half the occupancy
+    // workgroups: up to about those resident at once each takes the time of one
+    if (parts(N, 16) * s.blocks[role] * parts(o, 64) <= (wide ? 256 : 576))
+        return V == 1 || a >= 16 || plan->uvw_paths <= 2;
+    if (s.dmax == 1) return false;
+    double least = s.dmax == 3 ? (per_block <= 2 ? 32 : 24) : per_block < 6 ? 18 : per_block < 12 ? 12 : V == 1 ? 8 : 10;
+    if (wide) least *= 1.3;
+    // rows past the L2 caches, which the pairwise kernel reads once per output component
+    const int64_t row = (role == 0 ? s.nc1 : s.nco) * int64_t{4};
+    if (s.dmax > 3 && N * a * row > (int64_t{32} << 20)) least *= 0.65;
+    return static_cast<double>(a) >= least;
+}
 
 // grad_x2: the block kernel, but for degree 0 with few w (K = w), where the launch is all there is:
 // 65,536 edges, U = V = W = 2 60 against 80 us, W = 8 90 against 80.
@@ -596,7 +624,7 @@ extern "C" spingtp_status spingtp_forward_fully_connected(spingtp_plan plan, con
     if (cur != plan->device) return SPINGTP_ERR_INVALID_ARG;
     const int u = static_cast<int>(U), v = static_cast<int>(V), w = static_cast<int>(W);
     const hipError_t e =
-        use_blocks_mix(plan, N, U, V, W, U)
+        use_blocks_mix(plan, 0, N, U, V, W)
             ? spingtp::launch_uvwz_mix(static_cast<const float*>(x1), static_cast<const float*>(x2), weights,
                                        static_cast<float*>(out), N, u, v, w, V * W, W, 1, U * V * W, plan->uvwz,
                                        plan->d_uvwz, 0, static_cast<hipStream_t>(stream))
@@ -646,7 +674,7 @@ extern "C" spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, co
     const int u = static_cast<int>(U), v = static_cast<int>(V), w = static_cast<int>(W);
     const int64_t ps = U * V * W;
     hipError_t e = hipSuccess;
-    if (want1 && use_blocks_mix(plan, N, U, V, W, W))
+    if (want1 && use_blocks_mix(plan, 1, N, U, V, W))
         e = spingtp::launch_uvwz_mix(g, a2, weights, static_cast<float*>(grad_x1), N, w, v, u, 1, W, V * W, ps,
                                      plan->uvwz, plan->d_uvwz, 1, s);
     else if (want1)  // pairs (v, w) of x2 and grad_out, output channels u

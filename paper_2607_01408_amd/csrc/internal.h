@@ -303,6 +303,9 @@ bool build_uvw_table(int L1, int L2, int LO, const int* spins, int n_spins, unsi
 // One role's product and channel mixing: out[n][o][k] = sum_p sum_(a, b) weights[p-th block
 // + a sa + b sb + o so] R_p[n][(a, b)][k], R_p from xa [N][A][.] and xb [N][B][.]; the
 // output (N x O rows of nco floats) is written 0 first.
+// Whether that launch gives each workgroup one output component (of O output channels, weights
+// `so` apart) or kUvwChunk.
+bool uvw_one_component(int64_t N, int64_t O, int n_blocks, int max_d3, int64_t so);
 hipError_t launch_uvw_mix(const float* xa, const float* xb, const float* w, float* out, int64_t N, int A, int B, int O,
                           int64_t sa, int64_t sb, int64_t so, int64_t ps, const uint32_t* table, int n_blocks,
                           int max_d3, int nco, hipStream_t stream);

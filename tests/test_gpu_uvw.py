@@ -253,7 +253,7 @@ def test_uvw_backward_bitwise_deterministic():
     (1, 1, 2, S3, 5, 33, 2, 67),     # W not a multiple of 4 (4-byte weight loads), two v
     (3, 3, 3, S3, 9, 20, 1, 12),     # blocks of 7 slots
     (2, 2, 2, S5, 18, 6, 3, 18),     # five spins: invalid blocks of 3 slots, pairs with many paths
-    (2, 2, 2, S3, 20, 2, 40, 3),     # few channels, many v: the pairwise kernel for out and grad_W
+    (2, 2, 2, S3, 20, 2, 40, 3),     # few channels, many v: the pairwise kernels but for grad_x2
     (0, 1, 1, S3, 33, 65, 1, 129),   # blocks of one slot
 ])
 def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
@@ -265,6 +265,11 @@ def test_uvw_block_kernel_edges(L1, L2, LO, spins, N, U, V, W):
 
 
 @pytest.mark.parametrize("L1,L2,LO,spins,N,U,V,W", [
+    (2, 2, 2, S5, 18, 17, 3, 16),    # several v on the block kernels from 16 channels on: five spins
+    (3, 3, 3, S3, 7, 18, 2, 19),     # and blocks of 7 slots
+    (2, 2, 2, S3, 11, 16, 2, 15),    # one role either side of the line
+    (1, 1, 1, S3, 1537, 23, 1, 24),  # more workgroups than are resident: 24 channels for 3-slot blocks
+    (2, 2, 2, S3, 1025, 8, 1, 7),    # 8 for many paths per block
     (0, 0, 0, (0,), 9217, 2, 1, 8),  # degree 0: grad_x2 on the block kernel
     (0, 0, 0, (0,), 9217, 2, 1, 7),  # and on the pairwise kernel
     (2, 2, 2, S3, 40, 2, 16, 2),     # weight gradient: pairs (u, v) packed
