@@ -548,11 +548,13 @@ constexpr bool big_hoist_rows() {
 // unrolled groups fit the instruction cache.  131,072 units, fp32, owners and scalar loads ->
 // matrix units and registers: paper basis 0.438 -> 0.488 ms at L = 9, 0.533 -> 0.560 at 10,
 // 0.943 -> 0.834 at 11, 1.295 -> 1.037 at 12; parity basis 0.507 -> 0.514, 0.623 -> 0.591,
-// 1.083 -> 0.932, 1.285 -> 1.070; spin {0} 0.174 -> 0.226 at L = 11, 0.256 -> 0.255 at 12,
-// 0.307 -> 0.290 at 13.
-template <int L, bool SPIN>
+// 1.083 -> 0.932, 1.285 -> 1.070.  Spin {0}, us at 16,384 / 131,072 units, fp32: 34.0 / 257 ->
+// 37.7 / 256 at L = 12, 45.2 / 308 -> 43.3 / 292 at 13; bf16: 35.9 / 255 -> 38.9 / 267 at 12,
+// 39.3 / 283 -> 43.1 / 295 at 13, 46.9 / 351 -> 50.8 / 358 at 14, 51.1 / 393 -> 53.6 / 389 at 15 (one
+// unit 39.6 -> 34.9).
+template <int L, bool SPIN, bool F32>
 constexpr bool big_matrix_projection() {
-    return L >= (SPIN ? 11 : 12);
+    return L >= (SPIN ? 11 : F32 ? 13 : 15);
 }
 
 // PAR (spins only): the plan's basis is the parity-labelled one; a separate
@@ -581,7 +583,7 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
     using P = typename B::PS;
     constexpr Layout Y = B::Y;
     constexpr bool SPLIT = big_split_last<L, SPIN>();
-    constexpr bool MATRIX = big_matrix_projection<L, SPIN>();
+    constexpr bool MATRIX = big_matrix_projection<L, SPIN, F32>();
     static_assert(MATRIX || (B::K == 1 && !SPLIT), "the owners' form takes whole records of whole nodes");
     constexpr int TM1 = Y.TM + 1;
     constexpr int BO = (L + 1) * (L + 1);
