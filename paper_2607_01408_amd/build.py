@@ -10,13 +10,15 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libspingtp.so")
 SOURCES = ["plan.cpp", "api.cpp", "forward.hip", "forward_big_parity.hip", "forward_big_padded.hip",
-           "forward_big_parity_padded.hip", "forward_mfma.hip", "forward_pre.hip",
+           "forward_big_parity_padded.hip", "forward_big_parity_padded_minreg.hip", "forward_mfma.hip", "forward_pre.hip",
            "forward_pre_large.hip", "forward_pre_weighted.hip", "forward_direct.hip", "backward.hip", "backward_v1w.hip", "forward_uvw.hip",
            "uvw_blocks.hip", "channel_blocks.hip", "gram_x2.hip", "direct_unrolled_paper.hip", "direct_unrolled_paired.hip", "direct_unrolled_parity.hip"]
 # per-source additions
 # the compile-time tensor patterns take more constant-evaluation steps than the default limit
 _CONSTEXPR = ["-fconstexpr-steps=200000000"]
-EXTRA_FLAGS = {"direct_unrolled_paper.hip": _CONSTEXPR, "direct_unrolled_paired.hip": _CONSTEXPR,
+# the register-minimising scheduler, where it is the faster one (figures in the source)
+_MINREG = ["-mllvm", "-amdgpu-sched-strategy=iterative-minreg"]
+EXTRA_FLAGS = {"forward_big_parity_padded_minreg.hip": _MINREG, "direct_unrolled_paper.hip": _CONSTEXPR, "direct_unrolled_paired.hip": _CONSTEXPR,
                "direct_unrolled_parity.hip": _CONSTEXPR}
 
 # -packed-fp32-ops: no v_pk_{add,mul,fma}_f32 in generated code.

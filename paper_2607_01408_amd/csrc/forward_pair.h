@@ -886,5 +886,14 @@ constexpr int big_waves() {
     return 8;
 }
 
+// The entry of a mixed-degree kernel in the parity basis (spins {-1, 0, +1}).
+template <int L, typename TIO>
+constexpr KernelEntry big_parity_padded_entry() {
+    constexpr int W = big_waves<L, true>();
+    using B = BigShape<L, true, W>;
+    return KernelEntry{B::WAVES, B::UNITS, static_cast<int>(B::LDS_FLOATS * sizeof(float)), 3,
+                       &launch_big<L, true, W, false, true, TIO, true>, &launch_big<L, true, W, true, true, TIO, true>};
+}
+
 }  // namespace
 }  // namespace spingtp
