@@ -523,18 +523,20 @@ __device__ __forceinline__ void pair_publish_part(float* D, int sub, const float
 // Whether the last round splits its nodes' phi points over the idle waves, for the
 // degrees whose last round leaves half of them or more idle (11, 12, 13 and 16).
 // Measured on 131,072 units, fp32, without -> with: paper basis 0.904 -> 0.834 ms at
-// L = 11, 1.026 -> 1.037 at 12, 1.233 -> 1.223 at 13, 2.346 -> 2.272 at 16; parity basis
-// 0.928 -> 0.882, 1.079 -> 1.069, 1.286 -> 1.275, 2.477 -> 2.406.  Spin {0} has little
-// work per point: 0.226 -> 0.233, 0.256 -> 0.278, 0.292 -> 0.307, 0.559 -> 0.543.
-template <int L, bool SPIN>
+// L = 11, 1.233 -> 1.223 at 13, 2.346 -> 2.272 at 16; parity basis 0.928 -> 0.882,
+// 1.286 -> 1.275, 2.477 -> 2.406.  L = 12 has half of its waves idle there and the instantiations
+// differ by their registers: paper basis 1.025 -> 1.045 (both gradients 2.047 -> 2.024), parity 1.091
+// -> 1.079 (2.104 -> 2.152), mixed degrees (12, 2, 12), 65,536 units, 0.629 -> 0.607 (1.241 -> 1.191).
+// Spin {0} has little work per point: 0.226 -> 0.233, 0.256 -> 0.278, 0.292 -> 0.307, 0.559 -> 0.543.
+template <int L, bool SPIN, bool PAR, bool BWD, bool PAD>
 constexpr bool big_split_last() {
-    return L >= (SPIN ? 11 : 16);
+    return L >= (SPIN ? 11 : 16) && (L != 12 || PAD || PAR != BWD);
 }
 
 // Whether the staging loads may stay hoisted out of the round loop: the compiler then
 // loads every chunk's rows once per tile and keeps them in registers.  131,072 units,
-// fp32, paper basis, in the loop -> hoisted: 0.503 -> 0.488 ms at L = 9, 0.562 -> 0.571 at
-// 10, 0.876 -> 0.834 at 11, 1.080 -> 1.037 at 12, 1.223 -> 1.211 at 13 (parity basis
+// fp32, paper basis, in the loop -> hoisted: 0.503 -> 0.488 ms at L = 9, 0.598 -> 0.539 at
+// 10 (parity basis 0.627 -> 0.559), 0.876 -> 0.834 at 11, 1.080 -> 1.037 at 12, 1.223 -> 1.211 at 13 (parity basis
 // 1.275 -> 1.308); from there on they spill (1.425 -> 1.480 at 14, 2.272 -> 3.406 at 16),
 // and the scalar-spin kernels gain nothing.
 template <int L, bool SPIN>
@@ -547,7 +549,7 @@ constexpr bool big_hoist_rows() {
 // scalar loads.  With few orders per group the 16-row tiles are mostly padding and the
 // unrolled groups fit the instruction cache.  131,072 units, fp32, owners and scalar loads ->
 // matrix units and registers: paper basis 0.438 -> 0.488 ms at L = 9, 0.533 -> 0.560 at 10,
-// 0.943 -> 0.834 at 11, 1.295 -> 1.037 at 12; parity basis 0.507 -> 0.514, 0.623 -> 0.591,
+// 0.943 -> 0.834 at 11, 1.295 -> 1.037 at 12; parity basis 0.507 -> 0.514, 0.559 -> 0.590,
 // 1.083 -> 0.932, 1.285 -> 1.070.  Spin {0}, us at 16,384 / 131,072 units, fp32: 34.0 / 257 ->
 // 37.7 / 256 at L = 12, 45.2 / 308 -> 43.3 / 292 at 13; bf16: 35.9 / 255 -> 38.9 / 267 at 12,
 // 39.3 / 283 -> 43.1 / 295 at 13, 46.9 / 351 -> 50.8 / 358 at 14, 51.1 / 393 -> 53.6 / 389 at 15 (one
@@ -582,7 +584,7 @@ __global__ __launch_bounds__((BigShape<L, SPIN, W>::THREADS)) void spingtp_fwd_b
     constexpr bool F32 = std::is_same<TIO, float>::value;
     using P = typename B::PS;
     constexpr Layout Y = B::Y;
-    constexpr bool SPLIT = big_split_last<L, SPIN>();
+    constexpr bool SPLIT = big_split_last<L, SPIN, PAR, BWD, PAD>();
     constexpr bool MATRIX = big_matrix_projection<L, SPIN, F32>();
     static_assert(MATRIX || (B::K == 1 && !SPLIT), "the owners' form takes whole records of whole nodes");
     constexpr int TM1 = Y.TM + 1;
