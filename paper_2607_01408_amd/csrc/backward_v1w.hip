@@ -400,10 +400,18 @@ hipError_t launch_typed(const void* x1, const void* x2, const float* w, const vo
     const int64_t tiles = (C + kBw1wLanes - 1) / kBw1wLanes;
     int64_t groups = 0, epg = 0;
     int target = bw_target_groups(SHARED ? s.lds_floats : s.lds_unit_bwd);
-    // the block kernels where their LDS fits (faster at every shape measured: 88 entries, 1,024
-    // edges 44 -> 33 us; 2,048 edges of 683 entries 186 -> 85), with as many workgroups as are resident at once
-    // (never more edge ranges than the workspace is sized for)
-    const bool blocks_kernel = SHARED && cw != nullptr && cw_tab != nullptr && cw_bwd_lds_floats(*cw) <= kBw1wMaxLdsFloats;
+    // The block kernels where their LDS fits, with as many workgroups as are resident at once
+    // (never more edge ranges than the workspace is sized for).  Their cost per edge and tile
+    // has a fixed part (K, the barriers, the rows of 64 channels even if few are left) that
+    // tensors of a few dozen entries do not earn back once the chip is full.  us, spin {0}, entry
+    // lists against blocks: (1, 1, 1), 2,048 edges x 64 channels 56 / 35, 20,000 x 64 121 / 175,
+    // 1,024 x 200 35 / 46; (1, 2, 2) (37 entries) 2,048 x 64 62 / 35, 100,000 x 4 704 / 781; (3, 3, 3)
+    // (353 entries) 2,048 x 64 97 / 50, 100,000 x 16 3,101 / 1,356.  Many slots with an entry or two
+    // are as many entries of padding in the lists: (0, 2, 2), spins {-1, 0, 1}, 20,000 x 64 276 / 193.
+    const bool fits = SHARED && cw != nullptr && cw_tab != nullptr && cw_bwd_lds_floats(*cw) <= kBw1wMaxLdsFloats;
+    const bool blocks_kernel =
+        fits && (cw->nnz >= 84 || s.nc1 + s.nc2 + s.nco >= 48 ||
+                 N <= (cw->nnz < 32 ? 4096 : 32768) / std::max<int64_t>(1, tiles * tiles));
     if (blocks_kernel) target = std::min(target, 256 * std::min(2, kBw1wMaxLdsFloats / cw_bwd_lds_floats(*cw)));
     bw1w_groups(N, C, &groups, &epg, target);
     float* ws_x2 = ws;

@@ -526,3 +526,13 @@ def test_depthwise_bf16_roundings(shape, spins, basis, launches):
     err = rel_l2(host(y, N * C), ref)
     print(f"[depthwise] bf16 {shape} V={V} error {err:.3e}, one rounding {once:.3e}", flush=True)
     assert err <= 1.06 * np.sqrt(shares.sum()) * once
+
+
+@pytest.mark.parametrize("shape,N,C,dtype", [
+    ((1, 1, 1), 4096, 3, "fp32"), ((1, 1, 1), 4097, 3, "fp32"),    # 10 entries, one tile of 64 channels
+    ((1, 1, 1), 1024, 65, "bf16"), ((1, 1, 1), 1025, 65, "bf16"),  # two tiles
+    ((1, 2, 2), 8192, 66, "fp32"), ((1, 2, 2), 8193, 66, "fp32")])  # 37 entries, two tiles
+def test_channel_weighted_backward_routes(shape, N, C, dtype):
+    """Either side of the rule that gives the gradients of small tensors to the block kernels or to the entry
+    lists, all edges against the oracle."""
+    run_channel_weighted_backward(*shape, (0,), N, C, 0, dtype, seed=C)
