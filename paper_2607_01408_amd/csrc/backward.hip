@@ -138,8 +138,13 @@ int64_t row_length(const spingtp_plan_s* p) {
 // -> Gram: 65,536 edges x 1 channel 8.6 -> 16 (L = 1), 15 -> 35 (L = 2), 27 -> 94 (L = 3); x 8
 // channels 29 -> 21, 60 -> 40, 142 -> 103; 8,192 edges x 100 channels 67 -> 15, 107 -> 30,
 // 220 -> 69; one edge x 16,384 channels 2,739 -> 213, 4,904 -> 532, 5,568 -> 1,613.
-bool use_gram(const spingtp_plan_s* p, int64_t C) {
-    return p->d_gram != nullptr && C >= 8;
+// Short rows leave little to gain once the edges fill the chip: 300,000 edges, spin {0}, L = 1, 8 channels
+// 43 -> 81, 24 channels 115 -> 117; L = 0, 24 channels 57 -> 112; spins {-1, 0, 1}, L = 1, bf16, 8 channels
+// 68 -> 82, 12 channels 101 -> 99.  (A grid holds 2^32 work-items, 64 an edge here.)
+bool use_gram(const spingtp_plan_s* p, int64_t N, int64_t C) {
+    const int64_t nc = row_length(p);
+    const bool many = N > (nc <= 4 ? 16384 : 65536);
+    return p->d_gram != nullptr && C >= 8 && N < (int64_t{1} << 26) && (!many || (nc > 1 && C * nc > 96));
 }
 
 }  // namespace
@@ -194,7 +199,7 @@ extern "C" spingtp_status spingtp_backward_v1(spingtp_plan plan, const void* x1,
     }
     if (grad_x2 != nullptr) {
         if (workspace == nullptr || misaligned(workspace) || workspace_bytes < need) return SPINGTP_ERR_INVALID_ARG;
-        if (use_gram(plan, C)) {
+        if (use_gram(plan, N, C)) {
             if (x1 == nullptr || grad_out == nullptr || misaligned(x1) || misaligned(grad_out))
                 return SPINGTP_ERR_INVALID_ARG;
             int cur = -1;

@@ -287,3 +287,11 @@ def test_backward_v1_rules():
     mixed = Plan(3, 1, 2, S3, "fp32")
     assert lib.spingtp_backward_v1_workspace_size(mixed.handle, N, C, ctypes.byref(need)) == 0
     assert need.value == N * C * 3 * 4 * 4
+
+
+@pytest.mark.parametrize("L,spins,N,C,dtype", [(0, (0,), 16384, 9, "fp32"), (0, (0,), 16385, 9, "fp32"),
+                                               (1, (0,), 16385, 24, "bf16"), (1, (0,), 16385, 25, "fp32"),
+                                               (1, S3, 65537, 8, "fp32")])
+def test_backward_v1_short_rows(L, spins, N, C, dtype):
+    """Either side of the rule that leaves short rows of many edges to the per-channel products."""
+    run_backward_v1(L, spins, N, C, dtype, 0, seed=L + C)
