@@ -96,7 +96,7 @@ const UnrolledKernel* find_unrolled_paper(int L);
 const UnrolledKernel* find_unrolled_paired(int L);
 const UnrolledKernel* find_unrolled_parity(int L);
 // The values of the role's entries from the dense tensor, in the kernel's order; false where
-// the tensor has an entry that the kernel lacks.
+// the tensor's entries are not exactly the kernel's.
 bool unrolled_values(const UnrolledKernel& k, int role, int n1, int n2, int n3, const std::vector<double>& T,
                      std::vector<uint32_t>& words);
 

@@ -1096,7 +1096,9 @@ bool unrolled_values(const UnrolledKernel& k, int role, int n1, int n2, int n3, 
         std::memcpy(&w, &v, 4);
         words.push_back(w);
     }
-    return live == nonzero;
+    // an entry of value 0 (a path of weight 0) would shift the partial sums of the later ones and
+    // turn a non-finite input of that path into a NaN: the entry-list kernel has no such entries
+    return live == nonzero && live == static_cast<size_t>(k.n[role]);
 }
 
 bool build_uvw_blocks_table(int L1, int L2, int LO, const int* spins, int n_spins, unsigned flags,
