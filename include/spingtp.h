@@ -236,6 +236,10 @@ spingtp_status spingtp_forward_v1(spingtp_plan plan, const void* x1, const void*
  * degree <= 2 with spins {-1, 0, +1}, (1, 3, 3), degree <= 4 with spin {0}).
  * Plan creation with SPINGTP_CHANNEL_WEIGHTS fails with SPINGTP_ERR_UNSUPPORTED
  * when neither route nor the gradients' lists hold the shape.
+ * Non-finite inputs (block and entry-list kernels, here, in the depthwise form and in the
+ * gradients of both): an Inf or NaN reaches the results that the tensor has an entry with,
+ * and no others.  A block kernel forms a result that came out NaN again from the entries,
+ * so inputs with many of them take longer.
  * Gradients: spingtp_backward_v1_weighted.  Asynchronous, no allocation.
  */
 spingtp_status spingtp_forward_v1_weighted(spingtp_plan plan, const void* x1, const void* x2,
@@ -334,7 +338,7 @@ spingtp_status spingtp_forward_depthwise(spingtp_plan plan, const void* x1, cons
 /*
  * Gradients of spingtp_forward_depthwise: grad_x1 [N][C][...] (the sum over v),
  * grad_x2 [N][V][...] and grad_weights [V][C][n_paths] (fp32), each channel v's part
- * computed as by spingtp_backward_v1_weighted (deterministic).  The workspace
+ * computed as by spingtp_backward_v1_weighted (deterministic; bf16 grad_x1 rounds at every v).  The workspace
  * (spingtp_backward_depthwise_workspace_size, that of spingtp_backward_v1_weighted
  * for N, C) is reused by every v, so calls on one stream are ordered.  Rules as
  * spingtp_backward_v1_weighted.
@@ -458,8 +462,17 @@ spingtp_status spingtp_plan_upload_selftest_host(int L1, int L2, int Lout, const
  *   16-byte aligned, overwritten (0 in blocks no path reaches and in slots l < |s|).
  *   N, U, V, W >= 0, U, V, W <= 65536, U V <= 2^24; N W = 0 is a no-op, U V = 0 writes 0.
  * Needs an fp32 plan created with SPINGTP_FULLY_CONNECTED (else SPINGTP_ERR_UNSUPPORTED).
- * Products and sums in fp32: the per-path products R on the vector ALU, the channel
- * mixing on the matrix cores.  Asynchronous on `stream`, no allocation; deterministic.
+ * Products and sums in fp32.  Route: for degrees <= 3, but for few channels with several v or
+ * very many edges, the block kernels: the tensor is contracted with x2 once per edge (K_p, dense in
+ * a path's (k1, k3)) and the channel sums run on the input blocks on the matrix cores; else
+ * the per-path products R on the vector ALU and the channel mixing on the matrix cores.  The
+ * choice depends on N, U, V and W, so results of the same edge may differ in the last bits
+ * between calls of different sizes.
+ * Non-finite inputs: an Inf or NaN in x1, x2 (or grad_out, in the gradients) reaches the results
+ * that the tensor has an entry with, and no others; one in a weight at least the components of
+ * its path that have one.  A block kernel forms a result that came out NaN again from the
+ * entries, so inputs with many of them take longer.
+ * Asynchronous on `stream`, no allocation; deterministic.
  */
 spingtp_status spingtp_forward_fully_connected(spingtp_plan plan, const void* x1, const void* x2,
                                                const float* weights, void* out, int64_t N, int64_t U, int64_t V,
@@ -477,10 +490,11 @@ spingtp_status spingtp_forward_fully_connected(spingtp_plan plan, const void* x1
  *   that gradient.  Slots with l < |s| and blocks no path reaches get 0; with N = 0,
  *   grad_weights is 0.  U, V, W <= 65536 and U V, V W, U W <= 2^24.
  * Needs an fp32 plan created with SPINGTP_FULLY_CONNECTED (else SPINGTP_ERR_UNSUPPORTED).
- * fp32 products and sums (grad_x1 and grad_x2 on the forward's kernel with the tensor's
- * axes exchanged, grad_weights on the matrix cores with the edges as the reduction);
- * asynchronous on `stream`, no allocation; deterministic (every element has one owner
- * that sums in a fixed order).
+ * fp32 products and sums.  For degrees <= 3 the block kernels of the forward's route, each
+ * gradient by a rule of its own on the sizes; else grad_x1 on the forward's kernel with the
+ * tensor's axes exchanged, grad_x2 through W g, grad_weights on the matrix cores with the edges
+ * as the reduction.  Non-finite inputs as for the forward.  Asynchronous on `stream`, no
+ * allocation; deterministic (every element has one owner that sums in a fixed order).
  */
 spingtp_status spingtp_backward_fully_connected(spingtp_plan plan, const void* x1, const void* x2,
                                                 const float* weights, const void* grad_out, void* grad_x1,

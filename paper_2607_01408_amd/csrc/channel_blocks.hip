@@ -21,8 +21,10 @@
 // 157 -> 59 (the kernel alone); (1, 3, 3), 128 channels, parity basis: forward 55 -> 38, gradients
 // 184 -> 60.  One edge alone takes 11 us (25) and 22 us (73).  What bounds it now: the gradients'
 // weight and sum tiles leave room for one workgroup per CU in the paper basis, and half of its
-// cycles wait for LDS.  Non-finite inputs: K is dense over a path's (k1, k3), so a NaN in one
-// slot reaches every slot of the paths it enters.
+// cycles wait for LDS.  Non-finite inputs: K is dense over a path's (k1, k3), so a NaN that comes
+// out may be one of its zeros times an Inf or NaN; such results are formed again from the
+// tensor's entries (cw_entries), so an Inf or NaN reaches the slots that it has an entry with
+// and no others.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -100,15 +102,91 @@ struct CwRows {
     }
 };
 
-template <int THR, typename TIO>
+// sum over the tensor's entries of output slot k of W[p] value in[slot] x2[slot], from the blocks
+// (output blocks of the forward, x1 blocks of the gradients) whose references, items follow
+// at words 1 and 2 of `at`; nv second inputs x2v apart with weights wslice apart.  For results
+// that came out NaN (a spurious term is always a NaN; once the sum is one it stays so).
+// From global memory: other waves may be filling the LDS tiles with the next edge.
+template <typename TIO>
+__device__ __forceinline__ float cw_entries(const uint32_t* __restrict__ tab, const uint32_t* __restrict__ at, int n_blocks,
+                                            int k, const float* __restrict__ w, const TIO* __restrict__ in,
+                                            const TIO* __restrict__ x2, int nv, int64_t x2v, int64_t wslice) {
+    float s = 0.f;
+    for (int b = 0; b < n_blocks; ++b) {
+        const uint32_t* __restrict__ blk = tab + at[0] + 8 * b;
+        const int o = k - static_cast<int>(blk[0] & 0xffffu), d_o = static_cast<int>(blk[0] >> 16);
+        if (o < 0 || o >= d_o) continue;
+        const uint32_t* __restrict__ item = tab + at[2] + 4 * blk[3] + 4 * o;
+        uint32_t left = blk[5];  // references of width 1, 3, 5, 7 still to come, a byte each
+        int d_i = 1;
+        for (uint32_t j = blk[1]; j < blk[1] + blk[2]; ++j) {
+            while ((left & 0xffu) == 0) {
+                left >>= 8;
+                d_i += 2;
+            }
+            --left;
+            const uint32_t* __restrict__ ref = tab + at[1] + 4 * j;
+            for (int i = 0; i < d_i; ++i, item += 4 * d_o)
+                for (int t = 0; t < 2 && s == s; ++t) {
+                    const float val = __uint_as_float(item[1 + t]);
+                    if (val == 0.f) continue;
+                    const uint32_t k2 = t == 0 ? item[0] & 0xffffu : item[0] >> 16;
+                    const float a = val * cw_load(in + ref[1] + i);
+                    for (int v = 0; v < nv; ++v)
+                        s = fmaf(w[v * wslice + ref[0]], a * cw_load(x2 + v * x2v + k2), s);
+                }
+        }
+    }
+    return s;
+}
+
+// grad_W[channel c][path p] over the edges [n0, n1), likewise
+template <typename TIO>
+__device__ __forceinline__ float cw_weight_entries(const uint32_t* __restrict__ tab, int n_blocks, int p, int64_t n0,
+                                                   int64_t n1, int64_t C, int64_t c, const TIO* __restrict__ x1, int nc1,
+                                                   const TIO* __restrict__ g, int nco, const TIO* __restrict__ x2,
+                                                   int64_t x2s) {
+    float s = 0.f;
+    for (int b = 0; b < n_blocks; ++b) {
+        const uint32_t* __restrict__ blk = tab + tab[13] + 8 * b;
+        const int o = static_cast<int>(blk[0] & 0xffffu), d_o = static_cast<int>(blk[0] >> 16);
+        const uint32_t* __restrict__ item = tab + tab[15] + 4 * blk[3];
+        uint32_t left = blk[5];
+        int d_i = 1;
+        for (uint32_t j = blk[1]; j < blk[1] + blk[2]; ++j) {
+            while ((left & 0xffu) == 0) {
+                left >>= 8;
+                d_i += 2;
+            }
+            --left;
+            const uint32_t* __restrict__ ref = tab + tab[14] + 4 * j;
+            if (ref[0] == static_cast<uint32_t>(p))
+                for (int64_t n = n0; n < n1 && s == s; ++n)
+                    for (int i = 0; i < 2 * d_i * d_o; ++i) {
+                        const uint32_t* __restrict__ it = item + 4 * (i >> 1);
+                        const float val = __uint_as_float(it[1 + (i & 1)]);
+                        if (val == 0.f) continue;
+                        const uint32_t k2 = (i & 1) == 0 ? it[0] & 0xffffu : it[0] >> 16;
+                        s = fmaf(val * cw_load(x1 + (n * C + c) * nc1 + o + (i >> 1) % d_o),
+                                 cw_load(x2 + n * x2s + k2) * cw_load(g + (n * C + c) * nco + ref[1] + (i >> 1) / d_o), s);
+                    }
+            item += 4 * d_i * d_o;
+        }
+    }
+    return s;
+}
+
+// entries(r, c): the element from the tensor's entries, for those that are NaN here
+template <int THR, typename TIO, typename Entries>
 __device__ __forceinline__ void cw_unstage(TIO* __restrict__ dst, int nrows, int nc, int st, const float* src, int second,
-                                           int tid, bool add) {
+                                           int tid, bool add, const Entries& entries) {
     const int n = nrows * nc;
     int r = tid / nc, c = tid - r * nc;
     const int dr = THR / nc, dc = THR - dr * nc;
     for (int e = tid; e < n; e += THR) {
         float v = src[r * st + c];
         if (second) v += src[second + r * st + c];  // the blocks' second parts
+        if (__builtin_expect(v != v, 0)) v = entries(r, c);
         cw_store(dst + e, add ? cw_load(dst + e) + v : v);
         r += dr;
         c += dc;
@@ -316,7 +394,12 @@ __global__ __launch_bounds__(kCwFwdThreads, 4) void spingtp_cw_fwd_kernel(CwArgs
             }
         }
         __syncthreads();
-        cw_unstage<kCwFwdThreads>(out + row0 * nco, nch, nco, sto, O, parts > 1 ? kCwLanes * sto : 0, tid, P.add);
+        cw_unstage<kCwFwdThreads>(out + row0 * nco, nch, nco, sto, O, parts > 1 ? kCwLanes * sto : 0, tid, P.add,
+                                  [&](int r, int k) {
+                                      return cw_entries(tab, tab + 9, static_cast<int>(sched[kCwFwdWaves]), k,
+                                                        P.wts + (c0 + r) * np, x1 + (row0 + r) * nc1, x2 + n * P.x2s,
+                                                        NV, P.x2v, P.wslice);
+                                  });
     }
 }
 
@@ -505,7 +588,12 @@ __global__ __launch_bounds__(64 * NW, 4) void spingtp_cw_bwd_kernel(CwArgs P) {
                 else P.ws_x2[(blockIdx.y * P.N + n) * nc2 + k] = s;
             }
         }
-        cw_unstage<kCwBwdThreads>(gx1 + row0 * nc1, nch, nc1, st1, GX, parts > 1 ? kCwLanes * st1 : 0, tid, P.add);
+        cw_unstage<kCwBwdThreads>(gx1 + row0 * nc1, nch, nc1, st1, GX, parts > 1 ? kCwLanes * st1 : 0, tid, P.add,
+                                  [&](int r, int k) {
+                                      return cw_entries(tab, tab + 13, static_cast<int>(sched[kCwBwdWaves]), k,
+                                                        P.wts + (c0 + r) * np, g + (row0 + r) * nco, x2 + n * P.x2s, 1,
+                                                        0, 0);
+                                  });
         // (the next edge's rows go into X1, G and X2, which no wave reads past the barrier above;
         // its M and GX writes come after the next barrier)
     }
@@ -513,7 +601,12 @@ __global__ __launch_bounds__(64 * NW, 4) void spingtp_cw_bwd_kernel(CwArgs P) {
     if (n_end > n_begin)
         for (int i = tid; i < np * kCwLanes; i += kCwBwdThreads) {
             const int p = i >> 6, r = i & 63;
-            if (r < nch) P.ws_w[(blockIdx.x * static_cast<int64_t>(np) + p) * P.C + c0 + r] = GW[r * stw + p];
+            if (r >= nch) continue;
+            float s = GW[r * stw + p];
+            if (s != s)  // (see cw_entries)
+                s = cw_weight_entries(tab, static_cast<int>(sched[kCwBwdWaves]), p, n_begin, n_end, P.C, c0 + r, x1, nc1,
+                                      g, nco, x2, P.x2s);
+            P.ws_w[(blockIdx.x * static_cast<int64_t>(np) + p) * P.C + c0 + r] = s;
         }
 }
 

@@ -18,9 +18,10 @@
 //   forward and grad_x1 92 us each (404), grad_x2 122 (633), grad_W 150 (814);
 // the matrix products alone take 26 us each at the fp32 matrix rate.  What is left is vector
 // work (staging and the contraction, ten instructions per matrix instruction) in the first
-// three and the reads of the row blocks (1.8 GB through L2) in grad_W.  Non-finite inputs:
-// K is dense over a path's (k1, k3), so a NaN in one slot reaches every slot of the paths
-// it enters, also those it has no tensor entry with.
+// three and the reads of the row blocks in grad_W.  Non-finite inputs: K is dense over a path's
+// (k1, k3), so a NaN that comes out may be one of its zeros times an Inf or NaN; such results
+// are formed again from the tensor's entries (mix_entries), so an Inf or NaN reaches the slots
+// that it has an entry with and no others.
 //
 // Table (build_uvw_blocks_table): see internal.h.
 #include <hip/hip_runtime.h>
@@ -239,6 +240,37 @@ __device__ __forceinline__ void mix_stage(const MixArgs& P, const MixWave& M, in
     }
 }
 
+// A NaN from the dense products, again from the tensor's entries alone: an Inf or NaN meets
+// the zeros of K between slots that no entry couples, and 0 Inf is NaN.  Sums of values that are
+// finite or truly coupled never take this path (a spurious term is always a NaN), and once the
+// sum is a NaN it stays one.
+__device__ __forceinline__ float mix_entries(const MixArgs& P, const uint32_t* __restrict__ blk, int64_t n, int o,
+                                             int ko) {
+    const uint32_t* __restrict__ tab = P.tab;
+    const int d_out = static_cast<int>(hi16(blk[0]));
+    float s = 0.f;
+    for (int v = 0; v < P.V; ++v)
+        for (uint32_t st = blk[1]; st < blk[1] + blk[2]; ++st) {
+            const uint32_t* __restrict__ S = tab + tab[5 + 4 * P.role] + 4 * st;
+            const int o_in = static_cast<int>(lo16(S[0])), d_in = static_cast<int>(hi16(S[0]));
+            for (uint32_t j = S[1]; j < S[1] + S[2]; ++j) {
+                const uint32_t* __restrict__ ref = tab + tab[6 + 4 * P.role] + 4 * j;
+                for (int ki = 0; ki < d_in; ++ki) {
+                    const uint32_t* __restrict__ r = tab + ref[1] + 4 * (P.role == 0 ? ki * d_out + ko : ko * d_in + ki);
+                    for (int t = 0; t < 2; ++t) {
+                        const float val = __uint_as_float(r[2 * t + 1]);
+                        if (val == 0.f) continue;
+                        const float b = val * P.xb[(n * P.V + v) * P.ncb + r[2 * t]];
+                        const float* __restrict__ w = P.wt + ref[0] * P.ps + v * P.sv + static_cast<int64_t>(o) * P.so;
+                        for (int a = 0; a < P.A && s == s; ++a)
+                            s = fmaf(w[static_cast<int64_t>(a) * P.sa], P.xa[(n * P.A + a) * P.nca + o_in + ki] * b, s);
+                    }
+                }
+            }
+        }
+    return s;
+}
+
 template <int DO>
 __device__ __forceinline__ void mix_block(const MixArgs& P, const uint32_t* __restrict__ blk, float* sm) {
     const int tid = threadIdx.x;
@@ -297,12 +329,23 @@ __device__ __forceinline__ void mix_block(const MixArgs& P, const uint32_t* __re
     __syncthreads();
     const int on = P.O - o0 < no ? P.O - o0 : no;
     const int per = on * DO;
+    bool again = false;
     for (int i = tid; i < kZE * per; i += nthr) {
         const int er = i / per, rem = i - er * per;
         const int o = rem / DO, k = rem - o * DO;
         const int64_t n = n0 + er;
-        if (n < P.N) P.out[(n * P.O + o0 + o) * P.nco + o_out + k] = X[er * ste + rem];
+        const float v = X[er * ste + rem];
+        if (n < P.N) P.out[(n * P.O + o0 + o) * P.nco + o_out + k] = v;
+        again |= v != v;
     }
+    if (again)
+        for (int i = tid; i < kZE * per; i += nthr) {
+            const int er = i / per, rem = i - er * per;
+            const int o = rem / DO, k = rem - o * DO;
+            const int64_t n = n0 + er;
+            const float v = X[er * ste + rem];
+            if (n < P.N && v != v) P.out[(n * P.O + o0 + o) * P.nco + o_out + k] = mix_entries(P, blk, n, o0 + o, k);
+        }
 }
 
 // DM: the widest output block
@@ -357,6 +400,33 @@ __device__ __forceinline__ void grad_x2_path(const float (&w)[8], int nks, const
             for (int k2 = 0; k2 < D2; ++k2) acc[k2] = fmaf(T[(k1 * D3 + k) * D2 + k2], pr, acc[k2]);
         }
     }
+}
+
+// grad_x2[n, v, k2 of the block] from the tensor's entries (see mix_entries)
+__device__ __forceinline__ float grad_x2_entries(const GradX2Args& P, const uint32_t* __restrict__ blk, int64_t n, int v,
+                                                 int k2) {
+    const uint32_t* __restrict__ tab = P.tab;
+    const int d2 = static_cast<int>(hi16(blk[0]));
+    float s = 0.f;
+    for (uint32_t st = blk[1]; st < blk[1] + blk[2]; ++st) {
+        const uint32_t* __restrict__ S = tab + tab[5 + 8] + 4 * st;
+        const int o1 = static_cast<int>(lo16(S[0])), d1 = static_cast<int>(hi16(S[0]));
+        for (uint32_t j = S[1]; j < S[1] + S[2]; ++j) {
+            const uint32_t* __restrict__ ref = tab + tab[6 + 8] + 4 * j;
+            const int o3 = static_cast<int>(lo16(ref[3])), d3 = static_cast<int>(hi16(ref[3]));
+            for (int i = 0; i < d1 * d3; ++i) {
+                const float val = __uint_as_float(tab[ref[2] + i * d2 + k2]);
+                if (val == 0.f) continue;
+                for (int u = 0; u < P.U && s == s; ++u) {
+                    const float a = val * P.x1[(n * P.U + u) * P.nc1 + o1 + i / d3];
+                    const float* __restrict__ w =
+                        P.wt + ((static_cast<int64_t>(ref[0]) * P.U + u) * P.V + v) * static_cast<int64_t>(P.W);
+                    for (int c = 0; c < P.W; ++c) s = fmaf(w[c], a * P.g[(n * P.W + c) * P.nco + o3 + i % d3], s);
+                }
+            }
+        }
+    }
+    return s;
 }
 
 // grad_x2.  A workgroup owns 16 edges, one block of x2 and one channel v; wave (ug, ph)
@@ -463,7 +533,9 @@ __device__ __forceinline__ void grad_x2_block(const GradX2Args& P, const uint32_
         const int er = i / D2, k = i - er * D2;
         float s = 0.f;
         for (int w = 0; w < 8; ++w) s += sm[(w * kZE + er) * D2 + k];
-        if (n0 + er < P.N) P.gx2[((n0 + er) * P.V + v) * P.nc2 + o2 + k] = s;
+        if (n0 + er >= P.N) continue;
+        if (s != s) s = grad_x2_entries(P, blk, n0 + er, v, k);
+        P.gx2[((n0 + er) * P.V + v) * P.nc2 + o2 + k] = s;
     }
 }
 
@@ -499,6 +571,23 @@ constexpr int kGThreads = 64 * kGWaves;
 template <int D>
 __device__ __forceinline__ void load_row(const float* __restrict__ p, float (&v)[D]) {
     __builtin_memcpy(v, p, sizeof(v));
+}
+
+// grad_W[path][u][v][w] from the tensor's entries (see mix_entries)
+__device__ __forceinline__ float grad_w_entries(const GradWArgs& P, const uint32_t* __restrict__ unit,
+                                                const uint32_t* __restrict__ rec, int u, int v, int w) {
+    const int o1 = static_cast<int>(lo16(unit[0])), d1 = static_cast<int>(hi16(unit[0]));
+    const int o3 = static_cast<int>(lo16(unit[1])), d3 = static_cast<int>(hi16(unit[1]));
+    float s = 0.f;
+    for (int64_t n = 0; n < P.N && s == s; ++n)
+        for (int i = 0; i < d1 * d3; ++i)
+            for (int t = 0; t < 2; ++t) {
+                const float val = __uint_as_float(rec[4 * i + 2 * t + 1]);
+                if (val == 0.f) continue;
+                s = fmaf(val * P.x1[(n * P.U + u) * P.nc1 + o1 + i / d3] * P.x2[(n * P.V + v) * P.nc2 + rec[4 * i + 2 * t]],
+                         P.g[(n * P.W + w) * P.nco + o3 + i % d3], s);
+            }
+    return s;
 }
 
 // grad_W.  A workgroup owns up to kUvwzUnitPaths paths of one (rho1, rho3) pair, 32 channels
@@ -596,6 +685,7 @@ __device__ __forceinline__ void grad_w_unit(const GradWArgs& P, const uint32_t* 
     // the other waves' sums through LDS (16 x 64 floats each), added by wave 0 in wave order
     const int64_t VW = static_cast<int64_t>(P.V) * P.W;
     float* red = sm;
+    bool again = false;
 #pragma unroll
     for (int j = 0; j < kUvwzUnitPaths; ++j) {
         if (j >= np) break;
@@ -613,10 +703,22 @@ __device__ __forceinline__ void grad_w_unit(const GradWArgs& P, const uint32_t* 
                 float s = acc[j][i];
                 for (int w = 0; w < kGWaves - 1; ++w) s += red[(w * 16 + i) * 64 + lane];
                 const int u = u0 + 8 * (i >> 2) + 4 * half + (i & 3);
-                if (u < P.U) dst[u * VW] = s;
+                if (u < P.U) {
+                    dst[u * VW] = s;
+                    again |= s != s;
+                }
             }
         }
     }
+    if (again)
+#pragma unroll 1
+        for (int i = 0; i < 16 * np; ++i) {
+            const uint32_t* __restrict__ path = tab + tab[17] + 4 * (unit[2] + i / 16);
+            const int u = u0 + 8 * (i % 16 >> 2) + 4 * half + (i & 3);
+            if (u >= P.U) continue;
+            float* dst = P.gw + (static_cast<int64_t>(path[0]) * P.U + u) * VW + static_cast<int64_t>(v) * P.W + w0 + c;
+            if (*dst != *dst) *dst = grad_w_entries(P, unit, tab + path[1], u, v, w0 + c);
+        }
 }
 
 __global__ __launch_bounds__(kGThreads, 4) void spingtp_uvwz_grad_w_kernel(GradWArgs P) {

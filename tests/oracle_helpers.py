@@ -50,3 +50,23 @@ def valid_mask(spins, L):
         for l in range(abs(s), L + 1):
             m[si, l * l:(l + 1) ** 2] = True
     return m.ravel()
+
+
+def tensor_entries(L1, L2, LO, spins, basis):
+    """The nonzeros of the product's tensor: (k1, k2, k3, value, path) of each."""
+    from paper_2607_01408_amd import dense_tensor_host, paths_host
+
+    T = np.asarray(dense_tensor_host(L1, L2, LO, spins, basis))
+    block = [np.concatenate([np.repeat(i * (L + 1) + np.arange(L + 1), 2 * np.arange(L + 1) + 1)
+                             for i in range(len(spins))]) for L in (L1, L2, LO)]
+    path = {tuple(int(b) for b in t): p for p, t in enumerate(paths_host(L1, L2, LO, spins, basis))}
+    k1, k2, k3 = np.nonzero(np.abs(T) > 1e-12)
+    return [(a, b, c, T[a, b, c], path[block[0][a], block[1][b], block[2][c]]) for a, b, c in zip(k1, k2, k3)]
+
+
+def same_where_finite(got, ref, tol):
+    """got and ref are finite at the same places (some of each) and close there."""
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    assert np.array_equal(np.isfinite(got), fine)
+    assert np.linalg.norm(got[fine] - ref[fine]) <= tol * np.linalg.norm(ref[fine])

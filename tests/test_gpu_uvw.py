@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
-from tests.oracle_helpers import valid_mask
+from tests.oracle_helpers import same_where_finite, tensor_entries, valid_mask
 
 torch = pytest.importorskip("torch")
 
@@ -297,3 +297,47 @@ def test_uvw_more_edges_than_a_grid_of_edge_tiles():
         ref = t * a.double() * b.double()
         # one product: at most four roundings (T, and a product each with x, the weight and the other input)
         assert bool(((got.double() - ref).abs() <= 4 * 2.0 ** -24 * ref.abs() + 2.0 ** -149).all())
+
+
+@pytest.mark.parametrize("shape,spins,basis,N,U,V,W", [
+    ((2, 2, 2), S3, 0, 20, 18, 1, 20), ((1, 3, 3), S3, 2, 17, 16, 2, 17), ((2, 2, 2), S5, 2, 7, 3, 1, 5)])
+def test_uvw_non_finite_inputs(shape, spins, basis, N, U, V, W):
+    """An Inf or NaN reaches the slots that the tensor couples it with, and no others of its blocks: each poisoned
+    input against the sums over the tensor's entries."""
+    entries = tensor_entries(*shape, spins, basis)
+    plan = Plan(*shape, spins, "fp32", basis, fully_connected=True)
+    x1 = workloads.draw(shape[0], N, U, 97, "fp32", spins, "unit", "cuda")
+    x2 = workloads.draw(shape[1], N, V, 98, "fp32", spins, "unit", "cuda")
+    g = workloads.draw(shape[2], N, W, 99, "fp32", spins, "unit", "cuda")
+    w = torch.randn((plan.n_paths, U, V, W), generator=torch.Generator().manual_seed(4)).to("cuda")
+    k1, k2, k3, _, p = entries[len(entries) // 2]
+    for bad in range(4):
+        a, b, c, M = (t.clone() for t in (x1, x2, g, w))
+        if bad == 0:
+            a.view(N, U, -1)[1, 1, int(k1)] = float("inf")
+        elif bad == 1:
+            b.view(N, V, -1)[2, V - 1, int(k2)] = float("nan")
+        elif bad == 2:
+            c.view(N, W, -1)[1, 0, int(k3)] = -float("inf")
+        else:
+            M[p, 1, 0, 2] = float("inf")
+        got = [plan.forward_fully_connected(a, b, M), *plan.backward_fully_connected(a, b, M, c)]
+        torch.cuda.synchronize()
+        A, B, G = (t.reshape(N, t.shape[1], -1).double().cpu().numpy() for t in (a, b, c))
+        Md = M.double().cpu().numpy()
+        y, g1, g2, gw = np.zeros_like(G), np.zeros_like(A), np.zeros_like(B), np.zeros_like(Md)
+        with np.errstate(invalid="ignore"):
+            for i, j, k, t, q in entries:
+                for v in range(V):
+                    r = t * A[:, :, i] * B[:, v, None, j]                                  # [N, U]
+                    wg = G[:, None, :, k] * Md[q, None, :, v, :]                           # [N, U, W]
+                    y[:, :, k] += (r[:, :, None] * Md[q, None, :, v, :]).sum(axis=1)
+                    g1[:, :, i] += t * B[:, v, None, j] * wg.sum(axis=2)
+                    g2[:, v, j] += (t * A[:, :, i, None] * wg).sum(axis=(1, 2))
+                    gw[q, :, v, :] += (r[:, :, None] * G[:, None, :, k]).sum(axis=0)
+        for have, ref in zip(got, (y, g1, g2, gw)):
+            have = have.double().cpu().numpy().reshape(ref.shape)
+            if np.isfinite(ref).all():
+                assert np.isfinite(have).all() and np.linalg.norm(have - ref) <= TOL * np.linalg.norm(ref)
+            else:
+                same_where_finite(have, ref, TOL)

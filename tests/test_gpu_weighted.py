@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
+from tests.oracle_helpers import same_where_finite, tensor_entries
 
 torch = pytest.importorskip("torch")
 
@@ -536,3 +537,47 @@ def test_channel_weighted_backward_routes(shape, N, C, dtype):
     """Either side of the rule that gives the gradients of small tensors to the block kernels or to the entry
     lists, all edges against the oracle."""
     run_channel_weighted_backward(*shape, (0,), N, C, 0, dtype, seed=C)
+
+
+@pytest.mark.parametrize("shape,spins,basis,N,C,V,dtype", [
+    ((2, 2, 2), S3, 0, 5, 66, 1, "fp32"), ((2, 2, 2), S3, 2, 3, 9, 2, "bf16"), ((1, 3, 3), S3, 2, 4, 7, 3, "fp32"),
+    ((3, 3, 3), (0,), 0, 600, 3, 1, "fp32"), ((1, 1, 1), S3, 0, 6, 5, 1, "fp32")])
+def test_channel_weighted_non_finite_inputs(shape, spins, basis, N, C, V, dtype):
+    """An Inf or NaN reaches the slots that the tensor couples it with, and no others of its blocks: each poisoned
+    input against the sums over the tensor's entries.  (A path's entries do not fill its blocks.)"""
+    entries = tensor_entries(*shape, spins, basis)
+    P = len(paths_host(*shape, spins, basis))
+    plan = Plan(*shape, spins, dtype, basis, channel_weights=True)
+    x1 = workloads.draw(shape[0], N, C, 97, dtype, spins, "unit", "cuda")
+    x2 = workloads.draw(shape[1], N, V, 98, dtype, spins, "unit", "cuda")
+    g = workloads.draw(shape[2], N, C, 99, dtype, spins, "unit", "cuda")
+    w = torch.randn((V, C, P), generator=torch.Generator().manual_seed(4)).to("cuda")
+    k1, k2, k3, _, p = entries[len(entries) // 2]
+    for bad in range(4):
+        a, b, c, W = (t.clone() for t in (x1, x2, g, w))
+        if bad == 0:
+            a.view(N, C, -1)[1, 2, int(k1)] = float("inf")
+        elif bad == 1:
+            b.view(N, V, -1)[2, V - 1, int(k2)] = float("nan")
+        elif bad == 2:
+            c.view(N, C, -1)[1, 0, int(k3)] = -float("inf")
+        else:
+            W[0, 1, p] = float("inf")
+        got = [plan.forward_depthwise(a, b, W), *plan.backward_depthwise(a, b, W, c)]
+        torch.cuda.synchronize()
+        A, B, G = (t.reshape(N, t.shape[1], -1).double().cpu().numpy() for t in (a, b, c))
+        Wd = W.double().cpu().numpy()
+        y, g1, g2, gw = np.zeros_like(G), np.zeros_like(A), np.zeros_like(B), np.zeros_like(Wd)
+        with np.errstate(invalid="ignore"):
+            for i, j, k, t, q in entries:
+                for v in range(V):
+                    y[:, :, k] += Wd[v, :, q] * (t * A[:, :, i] * B[:, v, None, j])
+                    g1[:, :, i] += Wd[v, :, q] * (t * G[:, :, k] * B[:, v, None, j])
+                    g2[:, v, j] += (Wd[v, :, q] * (t * A[:, :, i] * G[:, :, k])).sum(axis=1)
+                    gw[v, :, q] += (t * A[:, :, i] * B[:, v, None, j] * G[:, :, k]).sum(axis=0)
+        for have, ref in zip(got, (y, g1, g2, gw)):
+            have = have.double().cpu().numpy().reshape(ref.shape)
+            if np.isfinite(ref).all():
+                assert np.isfinite(have).all() and rel_l2(have, ref) <= TOL[dtype]
+            else:
+                same_where_finite(have, ref, TOL[dtype])
