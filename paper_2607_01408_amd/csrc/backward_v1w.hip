@@ -49,11 +49,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstdint>
 
 #include "device_common.h"
 #include "internal.h"
+#include "lds_common.h"
 
 namespace spingtp {
 namespace {
@@ -376,23 +376,6 @@ __global__ __launch_bounds__(64 * kBw1wReduceWaves) void spingtp_bwd_v1w_reduce_
     }
 }
 
-// raise a kernel's dynamic LDS limit once per device (to the family's maximum); one
-// flag set per (TIO, TAG), i.e. per kernel
-template <typename TIO, int TAG>
-hipError_t raise_lds_limit(const void* kernel) {
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 static_cast<int>(kBw1wMaxLdsFloats * sizeof(float)));
-        if (e != hipSuccess) return e;
-        raised[dev].store(true, std::memory_order_release);
-    }
-    return hipSuccess;
-}
-
 template <typename TIO, bool SHARED>
 hipError_t launch_typed(const void* x1, const void* x2, const float* w, const void* g, void* gx1, void* gx2,
                         float* gw, float* ws, int64_t N, int64_t C, const Bw1wShape& s, const uint32_t* tab,
@@ -425,8 +408,7 @@ hipError_t launch_typed(const void* x1, const void* x2, const float* w, const vo
         const int lds_floats = SHARED ? s.lds_floats : s.lds_unit_bwd;
         const size_t bytes = static_cast<size_t>(lds_floats) * sizeof(float);
         if (bytes > 65536) {
-            const hipError_t e = raise_lds_limit<TIO, SHARED ? 1 : 2>(
-                reinterpret_cast<const void*>(&spingtp_bwd_v1w_kernel<TIO, SHARED>));
+            const hipError_t e = raise_lds_limit<&spingtp_bwd_v1w_kernel<TIO, SHARED>>();
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL((spingtp_bwd_v1w_kernel<TIO, SHARED>),
@@ -523,8 +505,7 @@ static hipError_t launch_fwd_typed(const void* x1, const void* x2, const float* 
     if (groups > 0x7fffffff || tiles > 0xffff) return hipErrorInvalidValue;
     const size_t bytes = static_cast<size_t>(lds_floats) * sizeof(float);
     if (bytes > 65536) {
-        const hipError_t e = raise_lds_limit<TIO, SHARED ? 3 + 2 * (NV - 1) : 4>(
-            reinterpret_cast<const void*>(&spingtp_fwd_cw_kernel<TIO, SHARED, NV>));
+        const hipError_t e = raise_lds_limit<&spingtp_fwd_cw_kernel<TIO, SHARED, NV>>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((spingtp_fwd_cw_kernel<TIO, SHARED, NV>),

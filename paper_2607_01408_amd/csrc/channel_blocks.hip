@@ -27,11 +27,11 @@
 // and no others.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cstdint>
 
 #include "device_common.h"
 #include "internal.h"
+#include "lds_common.h"
 
 namespace spingtp {
 namespace {
@@ -477,7 +477,6 @@ __device__ __forceinline__ void cw_bwd_block(const uint32_t* __restrict__ blk, c
 // M_p[k1, k3] of 16 rows (p, k1) and the 16 columns from slot col0 of the output (columns past
 // the spin's slots hold values no entry reads): v_mfma_f32_16x16x4f32 over the 64 channels.
 // B (the grad_out columns) is the same for all tiles of a spin.
-typedef float v4fm __attribute__((ext_vector_type(4)));
 
 // DM: the widest block of x1 and of the output; NW: waves (16 where one workgroup's LDS takes
 // more than half a CU's, else 8 so that two run: (2, 2, 2) paper basis 8 -> 16 waves 76 -> 59 us,
@@ -562,7 +561,7 @@ __global__ __launch_bounds__(64 * NW, 4) void spingtp_cw_bwd_kernel(CwArgs P) {
             const uint32_t rw = rows[16 * t + cl];
             const float* wr = Wt + q * stw + (rw & 0xffffu);
             const float* xr = X1 + q * st1 + (rw >> 16);
-            v4fm acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+            v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < 16; s += 2) {
                 acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[4 * s * stw] * xr[4 * s * st1], gc[4 * s * sto], acc0, 0, 0, 0);
@@ -610,25 +609,10 @@ __global__ __launch_bounds__(64 * NW, 4) void spingtp_cw_bwd_kernel(CwArgs P) {
         }
 }
 
-template <int TAG>
-hipError_t cw_raise(const void* kernel) {
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        raised[dev].store(true, std::memory_order_release);
-    }
-    return hipSuccess;
-}
-
 template <typename TIO, int NV, int DM>
 hipError_t cw_fwd(const CwArgs& P, dim3 grid, size_t bytes, hipStream_t stream) {
     if (bytes > 65536) {
-        const hipError_t e = cw_raise<(sizeof(TIO) == 4 ? 0 : 8) + NV + 100 * DM>(
-            reinterpret_cast<const void*>(&spingtp_cw_fwd_kernel<TIO, NV, DM>));
+        const hipError_t e = raise_lds_limit<&spingtp_cw_fwd_kernel<TIO, NV, DM>>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((spingtp_cw_fwd_kernel<TIO, NV, DM>), grid, dim3(kCwFwdThreads), bytes, stream, P);
@@ -649,8 +633,7 @@ hipError_t cw_fwd_nv(int nv, const CwArgs& P, dim3 grid, size_t bytes, hipStream
 template <typename TIO, int DM, int NW>
 hipError_t cw_bwd(const CwArgs& P, dim3 grid, size_t bytes, hipStream_t stream) {
     if (bytes > 65536) {
-        const hipError_t e = cw_raise<16 + sizeof(TIO) + 100 * DM + 1000 * NW>(
-            reinterpret_cast<const void*>(&spingtp_cw_bwd_kernel<TIO, DM, NW>));
+        const hipError_t e = raise_lds_limit<&spingtp_cw_bwd_kernel<TIO, DM, NW>>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((spingtp_cw_bwd_kernel<TIO, DM, NW>), grid, dim3(64 * NW), bytes, stream, P);

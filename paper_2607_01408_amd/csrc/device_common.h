@@ -24,14 +24,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     return static_cast<uint16_t>(u >> 16);
 }
 
-// Orders a wave's LDS accesses across its lanes: LDS executes a wave's instructions in
-// order, and the fence keeps the compiler from moving one lane's reads over another lane's
-// writes (the barrier alone orders no memory).
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int NC, int ST>
 __device__ __forceinline__ void put(float* dst, int e, float v) {
     const int u = e / NC;

@@ -22,6 +22,7 @@
 
 #include "device_common.h"
 #include "internal.h"
+#include "lds_common.h"
 #include "tensor_pattern.h"
 
 namespace spingtp {

@@ -39,6 +39,7 @@
 
 #include "device_common.h"
 #include "internal.h"
+#include "lds_common.h"
 
 namespace spingtp {
 namespace {

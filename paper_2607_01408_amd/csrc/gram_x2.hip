@@ -16,25 +16,14 @@
 
 #include <cstdint>
 
+#include "device_common.h"
 #include "internal.h"
 
 namespace spingtp {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float widen(float v) { return v; }
-__device__ __forceinline__ float widen(uint16_t v) { return __uint_as_float(static_cast<uint32_t>(v) << 16); }
 __device__ __forceinline__ void narrow(float v, float* p) { *p = v; }
-__device__ __forceinline__ void narrow(float v, uint16_t* p) {
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7f800000u) == 0x7f800000u) {
-        *p = static_cast<uint16_t>((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-        return;
-    }
-    u += 0x7fffu + ((u >> 16) & 1u);
-    *p = static_cast<uint16_t>(u >> 16);
-}
+__device__ __forceinline__ void narrow(float v, uint16_t* p) { *p = f32_to_bf16(v); }
 
 // NT neighbouring values of a row, which starts at any element: one load in fp32.
 typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -54,7 +43,7 @@ __device__ __forceinline__ void columns(const float* p, float (&v)[NT]) {
 template <int NT>
 __device__ __forceinline__ void columns(const uint16_t* p, float (&v)[NT]) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) v[i] = widen(p[i]);
+    for (int i = 0; i < NT; ++i) v[i] = bf16_to_f32(p[i]);
 }
 
 // tab: the table of build_gram_table.

@@ -26,11 +26,11 @@
 // Table (build_uvw_blocks_table): see internal.h.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cstdint>
 
 #include "device_common.h"
 #include "internal.h"
+#include "lds_common.h"
 
 namespace spingtp {
 namespace {
@@ -735,21 +735,6 @@ __global__ __launch_bounds__(kGThreads, 4) void spingtp_uvwz_grad_w_kernel(GradW
     }
 }
 
-// raise a kernel's dynamic LDS limit to 160 KB, once per device
-template <int TAG>
-hipError_t raise_limit(const void* kernel) {
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        raised[dev].store(true, std::memory_order_release);
-    }
-    return hipSuccess;
-}
-
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 size_t mix_lds(const UvwzShape& s, int ncb) {
@@ -773,7 +758,7 @@ int grad_x2_wch(const UvwzShape& s) {
 template <int DM>
 hipError_t launch_mix(const MixArgs& P, dim3 grid, size_t lds, hipStream_t stream) {
     if (lds > 65536) {
-        const hipError_t e = raise_limit<10 + DM>(reinterpret_cast<const void*>(&spingtp_uvwz_mix_kernel<DM>));
+        const hipError_t e = raise_lds_limit<&spingtp_uvwz_mix_kernel<DM>>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(spingtp_uvwz_mix_kernel<DM>, grid, dim3(kZThreads), lds, stream, P);
@@ -783,7 +768,7 @@ hipError_t launch_mix(const MixArgs& P, dim3 grid, size_t lds, hipStream_t strea
 template <int DM>
 hipError_t launch_grad_x2(const GradX2Args& P, dim3 grid, size_t lds, hipStream_t stream) {
     if (lds > 65536) {
-        const hipError_t e = raise_limit<20 + DM>(reinterpret_cast<const void*>(&spingtp_uvwz_grad_x2_kernel<DM>));
+        const hipError_t e = raise_lds_limit<&spingtp_uvwz_grad_x2_kernel<DM>>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(spingtp_uvwz_grad_x2_kernel<DM>, grid, dim3(kZThreads), lds, stream, P);
@@ -838,7 +823,7 @@ hipError_t launch_uvwz_grad_w(const float* x1, const float* x2, const float* g, 
                 s.nc2, s.nco, s.d1max, s.d3max, static_cast<unsigned>(tiles), table};
     const size_t lds = grad_w_lds(s);
     if (lds > 65536) {
-        const hipError_t e = raise_limit<2>(reinterpret_cast<const void*>(&spingtp_uvwz_grad_w_kernel));
+        const hipError_t e = raise_lds_limit<&spingtp_uvwz_grad_w_kernel>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(spingtp_uvwz_grad_w_kernel,

@@ -19,4 +19,4 @@ def test_wave_barriers_come_with_a_fence():
             helpers.append(os.path.basename(path))
             bare = re.findall(r'(?<!"wavefront"\);\n    )__builtin_amdgcn_wave_barrier\(\)', text)
             assert not bare, path
-    assert helpers == ["device_common.h"]  # one helper for all of them
+    assert helpers == ["lds_common.h"]  # one helper for all of them
