@@ -47,7 +47,18 @@ def kernel_sources(kname):
     main = {"spingtp_fwd_mfma_kernel": "forward_mfma.hip",
             "spingtp_fwd_direct_kernel": "forward_direct.hip"}.get(kname, "forward.hip")
     extra = ("forward_pair.h",) if main == "forward.hip" else ()
+    if kname == "spingtp_fwd_unrolled_kernel":
+        main, extra = "direct_unrolled.h", ("tensor_pattern.h", "lds_common.h")
     return tuple(_CSRC + f for f in (main, "device_common.h", "layout.h") + extra)
+
+
+def forward_kernel_name(family, L, spins, valu):
+    """The kernel of Plan.forward at L1 = L2 = Lout = L by its family; family 6 has the unrolled form
+    where the plan builds it (spins -2..2, L = 1 or 2, without the flag that keeps the entry lists)."""
+    if family == 6 and sorted(spins) == [-2, -1, 0, 1, 2] and 1 <= L <= 2 and not valu:
+        return "spingtp_fwd_unrolled_kernel"
+    return {1: "spingtp_fwd_kernel", 2: "spingtp_fwd_pair_kernel", 3: "spingtp_fwd_big_kernel",
+            4: "spingtp_fwd_mfma_kernel", 6: "spingtp_fwd_direct_kernel"}[family]
 
 
 def route_steps(L1, L2, LO, spin=True):
@@ -1059,8 +1070,7 @@ def run_main(args, pool):
     value = U / (ms_per_step / 1e3)
 
     kinfo = plan.kernel_info()
-    kname = {1: "spingtp_fwd_kernel", 2: "spingtp_fwd_pair_kernel", 3: "spingtp_fwd_big_kernel",
-             4: "spingtp_fwd_mfma_kernel", 6: "spingtp_fwd_direct_kernel"}[kinfo["family"]]
+    kname = forward_kernel_name(kinfo["family"], L, spins, args.valu)
     bytes_unit = hbm_bytes_per_unit(L, L, L, args.dtype, len(spins))
     if kinfo["family"] == 6:
         # the direct kernel: one product and one fma per nonzero of T (entries of its table)
