@@ -20,8 +20,9 @@
 // against the entry lists: (2, 2, 2), 64 channels, paper basis: forward 50 -> 23, gradients
 // 157 -> 59 (the kernel alone); (1, 3, 3), 128 channels, parity basis: forward 55 -> 38, gradients
 // 184 -> 60.  One edge alone takes 11 us (25) and 22 us (73).  What bounds it now: the gradients'
-// weight and sum tiles leave room for one workgroup per CU in the paper basis, and half of its
-// cycles wait for LDS.  Non-finite inputs: K is dense over a path's (k1, k3), so a NaN that comes
+// weight and sum tiles leave room for one workgroup per CU in the paper basis, and its waves
+// stand at a wait or barrier for 55 to 61 % of their cycles (the vector ALU issues on 32 to 39 %;
+// 2 to 5 % wait for the LDS pipe to take an instruction).  Non-finite inputs: K is dense over a path's (k1, k3), so a NaN that comes
 // out may be one of its zeros times an Inf or NaN; such results are formed again from the
 // tensor's entries (cw_entries), so an Inf or NaN reaches the slots that it has an entry with
 // and no others.
@@ -561,15 +562,23 @@ __global__ __launch_bounds__(64 * NW, 4) void spingtp_cw_bwd_kernel(CwArgs P) {
             const uint32_t rw = rows[16 * t + cl];
             const float* wr = Wt + q * stw + (rw & 0xffffu);
             const float* xr = X1 + q * st1 + (rw >> 16);
-            v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+            // eight chains of 8 channels (four at a time) and their tree: one or two long chains
+            // round more than the entry lists' tree over the lanes
+            v4f sum[2];
 #pragma unroll
-            for (int s = 0; s < 16; s += 2) {
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[4 * s * stw] * xr[4 * s * st1], gc[4 * s * sto], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[4 * (s + 1) * stw] * xr[4 * (s + 1) * st1],
-                                                            gc[4 * (s + 1) * sto], acc1, 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                v4f acc[4];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int s = 8 * h + i;
+                    const v4f c = i < 4 ? v4f{0.f, 0.f, 0.f, 0.f} : acc[i & 3];
+                    acc[i & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[4 * s * stw] * xr[4 * s * st1], gc[4 * s * sto],
+                                                                      c, 0, 0, 0);
+                }
+                sum[h] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) M[t * 256 + (4 * q + r) * 16 + cl] = acc0[r] + acc1[r];
+            for (int r = 0; r < 4; ++r) M[t * 256 + (4 * q + r) * 16 + cl] = sum[0][r] + sum[1][r];
         }
         __syncthreads();
         // gx2: 16 lanes per x2 slot take its entries in turn; their sums are added by shuffles

@@ -581,3 +581,21 @@ def test_channel_weighted_non_finite_inputs(shape, spins, basis, N, C, V, dtype)
                 assert np.isfinite(have).all() and rel_l2(have, ref) <= TOL[dtype]
             else:
                 same_where_finite(have, ref, TOL[dtype])
+
+
+@pytest.mark.parametrize("big", [0, 5, 31, 63])
+def test_channel_weighted_grad_x2_channel_sum(big):
+    """grad_x2 adds the 64 channels of a tile in short chains: one product of 1 and 63 of 2^-25, each below half a
+    unit in the last place of 1.  Chains of 8 and a tree over them (3 more additions) lose at most 8 + 3 roundings of
+    2^-24, the tensor's value and its product one each; a chain of 32 behind the 1 loses 31 / 2 of them."""
+    N, C = 3, 64
+    plan = Plan(0, 0, 0, (0,), "fp32", 0, channel_weights=True)
+    x1 = torch.full((N, C, 1, 1), 2.0 ** -25, device="cuda")
+    x1[:, big] = 1.0
+    x2, g = torch.ones((N, 1, 1, 1), device="cuda"), torch.ones((N, C, 1, 1), device="cuda")
+    w = torch.ones((C, 1), device="cuda")
+    gx2 = plan.backward_v1_weighted(x1, x2, w, g)[1]
+    torch.cuda.synchronize()
+    [(_, _, _, t, _)] = tensor_entries(0, 0, 0, (0,), 0)
+    ref = t * (1 + 63 * 2.0 ** -25)
+    assert float((gx2.double().cpu() / ref - 1).abs().max()) <= 13 * 2.0 ** -24
