@@ -259,12 +259,15 @@ struct CwPathRows {
             cw_k_row<DO>(kr + i * KD, k[i]);
         }
     }
+    // (the path's own sum first: one chain over all paths and slots rounds more than the entry
+    // lists' two)
     __device__ __forceinline__ void add(float (&out)[DO]) const {
 #pragma unroll
-        for (int i = 0; i < DI; ++i) {
-            const float y = w * x[i];
+        for (int c = 0; c < DO; ++c) {
+            float y = x[0] * k[0][c];
 #pragma unroll
-            for (int c = 0; c < DO; ++c) out[c] = fmaf(y, k[i][c], out[c]);
+            for (int i = 1; i < DI; ++i) y = fmaf(x[i], k[i][c], y);
+            out[c] = fmaf(w, y, out[c]);
         }
     }
 };
