@@ -258,9 +258,11 @@ spingtp_status spingtp_forward_v1_weighted(spingtp_plan plan, const void* x1, co
  *   workspace: device memory of spingtp_backward_v1_weighted_workspace_size bytes
  *     or more, 4-byte aligned, overwritten (partial sums over channel tiles and
  *     edge ranges, added in a fixed order, so results do not depend on scheduling).
- * All three outputs are required and must not overlap the inputs.  Kernel: one
- * wave per 64-channel tile and range of edges walks the tensor's nonzeros in three
- * orders (by k1, by k2, by path) with the tile's weights in LDS; built where the
+ * All three outputs are required and must not overlap the inputs.  Kernel: for
+ * degrees <= 3 the block kernel (see spingtp_forward_v1_weighted) where its tiles fit 160 KB,
+ * but for tensors of a few dozen nonzeros on many edges; else four
+ * waves per 64-channel tile and range of edges walk the tensor's nonzeros in three
+ * orders (by k1, by k2, by path) with the tile's weights in LDS.  Built where the
  * slot counts and the path count are <= 1022 and the LDS tile fits 160 KB (the
  * depthwise runtime table's shapes), otherwise SPINGTP_ERR_UNSUPPORTED, as for
  * plans created without SPINGTP_CHANNEL_WEIGHTS.  Asynchronous on `stream`, no
@@ -397,7 +399,8 @@ spingtp_status spingtp_backward(spingtp_plan plan, const void* x1, const void* x
  * `workspace` ([N][C][n_spins (L2+1)^2], the plan's dtype), then a second kernel
  * sums them over c in order (fp32 sums; bf16 output rounded to nearest even).
  * On plans whose v1 kernel is the precontracted one, with rows of at most 48 slots and
- * C >= 8, grad_x2 is formed from the edge's sums of x1[k1] grad_out[k3] over the channels
+ * C >= 8 (short rows on many edges excepted), grad_x2 is formed from the edge's sums of
+ * x1[k1] grad_out[k3] over the channels
  * (fp32 throughout, one rounding for bf16 output); the workspace is not written then.
  * On plans whose gradients run on the direct kernel (see spingtp_backward), both
  * steps use its role tables instead (grad_x1 with x2 read once per edge), except
